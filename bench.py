@@ -44,18 +44,15 @@ HBM_PEAK_GBS = 8000.0
 # Valid only for the kernel sources it was measured on.
 WGRAD_TRAFFIC = {"sources_sha256": "5b2c7ed08ef49c4e14822aaf57262fccd09a2efe914ec142e5b6281a7b7cd87c",
                  "bytes_per_launch": 725832891}
-TRAFFIC_SOURCES = ("gemm.hip", "common.h", "launch.h")
+TRAFFIC_SOURCES = ("gemm.hip", "gemm_dl.h", "common.h", "launch.h")
 
 
 def wgrad_kernel_name(cfg, epi):
     """The kernel the weight-gradient GEMMs (k = tokens of a micro-batch) launch."""
     if cfg.dtype != "bf16":
-        return f"gemm_kernel<f32, A not k-contiguous, B not k-contiguous, epilogue {epi}> (weight gradients)"
-    if (cfg.batch * cfg.seq_len) % 128 == 0:
-        return (f"gemm_p4_kernel<A not k-contiguous, B not k-contiguous, epilogue {epi}> (weight gradients; "
-                "four waves of 128x128 with double-buffered fragments, four-stage direct-to-LDS pipeline)")
-    return (f"gemm_p3_kernel<A not k-contiguous, B not k-contiguous, epilogue {epi}> (weight gradients; "
-            "sixteen waves, four-stage direct-to-LDS pipeline)")
+        return f"gemm_dl_kernel<f32, A not k-contiguous, B not k-contiguous, epilogue {epi}> (weight gradients)"
+    return (f"gemm_dl_kernel<bf16, A not k-contiguous, B not k-contiguous, epilogue {epi}> (weight gradients; "
+            "four waves with double-buffered fragments, four-stage direct-to-LDS pipeline)")
 
 
 def kernel_sources_sha256():

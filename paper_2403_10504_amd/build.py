@@ -22,7 +22,8 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libatom.so")
 ARCH = "gfx950"
 
-HIP_SOURCES = ["gemm.hip", "attention.hip", "attention_f32.hip", "rowops.hip", "runtime.cpp", "nodes.cpp", "schedule.cpp",
+HIP_SOURCES = ["gemm.hip", "gemm_dl_256.hip", "gemm_dl_192.hip", "gemm_dl_256x128.hip", "gemm_dl_128.hip", "gemm_dl_64.hip", "gemm_dl_f32.hip",
+               "attention.hip", "attention_f32.hip", "rowops.hip", "runtime.cpp", "nodes.cpp", "schedule.cpp",
                "host_accum.cpp", "transfer.cpp", "capi_kernels.cpp"]
 # per-source optimisation level (see attention_f32.hip)
 OPT = {"attention_f32.hip": "-O1"}

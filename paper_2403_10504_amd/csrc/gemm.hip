@@ -10,19 +10,14 @@
 //   data grad dx = dy W   : A = dy (KC),          B = W  (not KC)
 //   weight grad dW = dy^T x: A = dy (not KC),      B = x  (not KC)
 //
-// Tiling: a BM x BN output tile per workgroup of WM x WN waves (256x256 with
-// 16 waves of 64x64 for big problems: four waves per SIMD hide the global
-// and LDS latency better than eight waves of 64x128, measured +16 %;
-// 128x128 with 4 waves otherwise), 128-byte k tile (64 bf16 or 32 fp32)
-// double-buffered in LDS.  Every operand is staged in LDS with k contiguous
-// (rows padded to 144 bytes to spread ds_read_b128 over the banks); operands
-// that are not k-contiguous in memory are transposed while being written to
-// LDS.  Each lane reads 16x16x32 MFMA fragments (see common.h).  Larger
-// per-wave tiles raise the MFMA work per byte read from LDS.  Workgroup ids
-// are remapped so that neighbouring output tiles, which share A rows or B
-// columns, run on the same XCD (each XCD has its own L2).  Problems with few
-// output tiles and a long k (weight gradients of narrow layers) split k over
-// workgroups; the fp32 partials are summed in split order by a second kernel,
+// The direct-load kernel (gemm_dl.h) takes every problem whose 16-byte chunks
+// are whole; choose() picks its tile and a split over k.  The kernel here is
+// for the rest (odd row counts or leading dimensions): 128x128 tiles of four
+// waves, a 128-byte k tile (64 bf16 or 32 fp32) staged through registers and
+// double-buffered in LDS with k contiguous (rows padded to 144 bytes to
+// spread ds_read_b128 over the banks; operands that are not k-contiguous in
+// memory are transposed while being written to LDS).  A split over k writes
+// fp32 partials that a second kernel sums in split order before the epilogue,
 // so the result does not depend on scheduling.
 #include <algorithm>
 #include <type_traits>
@@ -35,19 +30,9 @@ namespace {
 
 constexpr int ROW_BYTES = 128, PITCH_BYTES = 144;
 
-// Workgroup tile BM x BN computed by WM x WN waves, each owning a
-// (BM/WM) x (BN/WN) block of 16x16 MFMA tiles.
-#ifndef ATOM_GEMM_CFG
-#define ATOM_GEMM_CFG 256, 256, 4, 4
-#endif
-template <int BM_, int BN_, int WM_, int WN_>
-struct Cfg {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
-  static constexpr int NT = 64 * WM_ * WN_;
-  static constexpr int TM = BM_ / (16 * WM_), TN = BN_ / (16 * WN_);
-};
-using Big = Cfg<ATOM_GEMM_CFG>;   // large problems
-using Small = Cfg<128, 128, 2, 2>; // few output tiles
+// Workgroup tile BM x BN computed by 2 x 2 waves, each owning a
+// (BM/2) x (BN/2) block of 16x16 MFMA tiles.
+constexpr int BM = 128, BN = 128, NT = 256, TM = BM / 32, TN = BN / 32;
 
 template <typename T>
 struct Tile {
@@ -255,31 +240,19 @@ __device__ __forceinline__ void epilogue4(const GemmArgs& g, int m, int nb, floa
   }
 }
 
-// Epilogues that read an element operand (C itself, the fp32 residual or the
-// saved pre-activation) and epilogues that add the bias.
-template <int EPI>
-constexpr bool epi_reads_elem() {
-  return EPI == EPI_ACC_F32 || EPI == EPI_BIAS_RESID || EPI == EPI_GELU_BWD;
-}
-template <int EPI>
-constexpr bool epi_has_bias() {
-  return EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESID;
-}
-
 // One output tile per workgroup (blockIdx.x), one k range per split
 // (blockIdx.y).  With splits > 1 the raw fp32 sums go to the workspace
 // ws[split][M][N] and splitk_reduce applies the epilogue.
-template <typename T, bool AKC, bool BKC, int EPI, class CF>
-__global__ void __launch_bounds__(CF::NT) gemm_kernel(GemmArgs g) {
+template <typename T, bool AKC, bool BKC, int EPI>
+__global__ void __launch_bounds__(NT) gemm_kernel(GemmArgs g) {
   using TL = Tile<T>;
-  constexpr int BM = CF::BM, BN = CF::BN, NT = CF::NT, TM = CF::TM, TN = CF::TN;
   __shared__ __attribute__((aligned(16))) T As[2][BM * TL::PITCH];
   __shared__ __attribute__((aligned(16))) T Bs[2][BN * TL::PITCH];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const int wm = w / CF::WN, wn = w % CF::WN;
+  const int wm = w >> 1, wn = w & 1;
 
   // Tile order: XCD-aware remap (consecutive ids go round-robin over the 8
   // XCDs, so give each XCD a contiguous range), then groups of 8 row-tiles
@@ -396,8 +369,7 @@ __global__ void __launch_bounds__(CF::NT) gemm_kernel(GemmArgs g) {
   }
 }
 
-// Sum of the split partials in split order, then the epilogue (store in the
-// element type, store fp32, or add to fp32).
+// Sum of the split partials in split order, then the epilogue.
 template <typename T, int EPI>
 __global__ void __launch_bounds__(256) splitk_reduce(GemmArgs g, int splits) {
   const int64_t MN = static_cast<int64_t>(g.M) * g.N;
@@ -424,13 +396,33 @@ __global__ void __launch_bounds__(256) splitk_reduce(GemmArgs g, int splits) {
   }
 }
 
-template <typename T, bool AKC, bool BKC, class CF>
-hipError_t launch_cfg(const GemmArgs& g, int epi, int splits, hipStream_t s) {
-  const int tiles = ((g.M + CF::BM - 1) / CF::BM) * ((g.N + CF::BN - 1) / CF::BN);
-  dim3 grid(tiles, splits), block(CF::NT);
+template <typename T>
+hipError_t launch_reduce(const GemmArgs& g, int epi, int splits, hipStream_t s) {
+  const int64_t MN = static_cast<int64_t>(g.M) * g.N;
+  dim3 rgrid(static_cast<unsigned>((MN + 1023) / 1024)), rblock(256);
   switch (epi) {
 #define ATOM_CASE(E) \
-  case E: hipLaunchKernelGGL((gemm_kernel<T, AKC, BKC, E, CF>), grid, block, 0, s, g); break;
+  case E: hipLaunchKernelGGL((splitk_reduce<T, E>), rgrid, rblock, 0, s, g, splits); break;
+    ATOM_CASE(EPI_STORE)
+    ATOM_CASE(EPI_STORE_F32)
+    ATOM_CASE(EPI_ACC_F32)
+    ATOM_CASE(EPI_BIAS)
+    ATOM_CASE(EPI_BIAS_GELU)
+    ATOM_CASE(EPI_BIAS_RESID)
+    ATOM_CASE(EPI_GELU_BWD)
+#undef ATOM_CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <typename T, bool AKC, bool BKC>
+hipError_t launch_small(const GemmArgs& g, int epi, int splits, hipStream_t s) {
+  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  dim3 grid(tiles, splits), block(NT);
+  switch (epi) {
+#define ATOM_CASE(E) \
+  case E: hipLaunchKernelGGL((gemm_kernel<T, AKC, BKC, E>), grid, block, 0, s, g); break;
     ATOM_CASE(EPI_STORE)
     ATOM_CASE(EPI_STORE_F32)
     ATOM_CASE(EPI_ACC_F32)
@@ -443,643 +435,120 @@ hipError_t launch_cfg(const GemmArgs& g, int epi, int splits, hipStream_t s) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
-  const int64_t MN = static_cast<int64_t>(g.M) * g.N;
-  dim3 rgrid(static_cast<unsigned>((MN / 4 + 255) / 256 + 1)), rblock(256);
-  switch (epi) {
-    case EPI_STORE: hipLaunchKernelGGL((splitk_reduce<T, EPI_STORE>), rgrid, rblock, 0, s, g, splits); break;
-    case EPI_STORE_F32: hipLaunchKernelGGL((splitk_reduce<T, EPI_STORE_F32>), rgrid, rblock, 0, s, g, splits); break;
-    case EPI_ACC_F32: hipLaunchKernelGGL((splitk_reduce<T, EPI_ACC_F32>), rgrid, rblock, 0, s, g, splits); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return launch_reduce<T>(g, epi, splits, s);
 }
 
-// ------------------------------------------------------------ pipelined
-// bf16 GEMM for large problems with a four-stage LDS pipeline fed by direct
-// global-to-LDS loads (global_load_lds_dwordx4: no staging registers, no LDS
-// store instructions).  256x256 output tile, 16 waves of 64x64, k tile of 32.
-// Iteration t waits for its own stage (the loads of the two later stages may
-// still be in flight), synchronises the workgroup, starts the loads of tile
-// t+3 into the stage iteration t-1 has just finished reading, then computes.
-// Each stage is a separate LDS array and the stage rotation is unrolled, so
-// the compiler sees which array every load and read touches and inserts no
-// waits of its own between them.
-//
-// LDS layouts (16-byte chunks are XOR-swizzled so that fragment reads are
-// free of bank conflicts; a direct load writes 1 KB per wave contiguously, so
-// the swizzle is applied to the global address each lane loads):
-//   k-contiguous operand  [256 rows][32 k]: row r, chunk c at slot c ^ ((r>>1)&3);
-//                         fragments by ds_read_b128.
-//   other operand         [32 k][256 rows]: k row k, chunk c (8 rows) at slot
-//                         c ^ tr_swz(k); fragments by two ds_read_b64_tr_b16,
-//                         each transposing a 4 (k) x 16 (rows) block across 16
-//                         lanes.
-// Rows beyond the operand are clamped to its last valid row (or 8-row block),
-// so they read finite data that only reaches output rows or columns that are
-// never stored; k must be a multiple of 32.
-#ifndef ATOM_GEMM_PIPE
-#define ATOM_GEMM_PIPE 1
-#endif
-#ifndef P3_ROUNDS
-#define P3_ROUNDS 1
-#endif
-namespace p3 {
-constexpr int BM = 256, BN = 256, BK = 32, WM = 4, WN = 4, NT = 64 * WM * WN;
-constexpr int TM = BM / (16 * WM), TN = BN / (16 * WN);
-constexpr int OPB = BM * BK * 2;  // bytes of one operand tile in one stage
-
-
-// Workgroup barrier that is also a compiler barrier for memory accesses.
-// This wave's LDS reads must have completed (lgkmcnt) before it arrives, as
-// the loads issued right after the barrier overwrite the stage they read;
-// unlike __syncthreads it does not drain the direct loads still in flight.
-__device__ __forceinline__ void barrier_only() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// Swizzle of the transposed-read layout: a ds_read_b64_tr_b16 serves 32
-// lanes per LDS cycle, i.e. the k rows K0..K0+3 and K0+8..K0+11 of two
-// 16-lane groups; 2 (k & 3) + 8 ((k >> 3) & 1) puts their 16 chunks on
-// distinct banks (measured: no conflicts, against two conflict cycles per
-// read with 2 (k & 3) alone).
-__device__ __forceinline__ int tr_swz(int k) { return 2 * (k & 3) + 8 * ((k >> 3) & 1); }
-
-// Per-thread source of its one 16-byte chunk of an operand tile.
-template <bool KC>
-struct Src {
-  const bf16_t* p;  // address for k0 = 0
-  int64_t kstep;    // elements to advance per k tile
-  __device__ void init(const bf16_t* X, int64_t ld, int r0, int Rlim, int tid) {
-    if constexpr (KC) {
-      const int r = tid >> 2, slot = tid & 3;
-      const int c = slot ^ ((r >> 1) & 3);
-      const int rr = min(r0 + r, Rlim - 1);
-      p = X + static_cast<int64_t>(rr) * ld + c * 8;
-      kstep = BK;
-    } else {
-      const int k = tid >> 5, slot = tid & 31;
-      const int c = slot ^ tr_swz(k);
-      const int m = min(r0 + c * 8, Rlim - 8);
-      p = X + static_cast<int64_t>(k) * ld + m;
-      kstep = static_cast<int64_t>(BK) * ld;
-    }
-  }
-  __device__ __forceinline__ void load(uint8_t* stage, int kt, int w) const {
-    lds_dma16(p + kt * kstep, __builtin_amdgcn_readfirstlane(lds_offset(stage) + w * 1024));
-  }
-};
-
-// Byte offsets inside a stage of this lane's fragment reads of tile rows
-// row0..row0+15 (one for k-contiguous operands, two transposed reads
-// otherwise); loop-invariant, computed once.
-template <bool KC>
-struct FragOff {
-  uint32_t o[KC ? 1 : 2];
-  __device__ void init(int row0, int lane) {
-    const int r = lane & 15, g = lane >> 4;
-    if constexpr (KC) {
-      const int row = row0 + r;
-      o[0] = row * 64 + 16 * (g ^ ((row >> 1) & 3));
-    } else {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k = 8 * g + 4 * h + (r >> 2);
-        const int m = row0 + 4 * (r & 3);
-        o[h] = k * 512 + 16 * ((m >> 3) ^ tr_swz(k)) + 8 * (r & 1);
-      }
-    }
-  }
-};
-
-// Fragment (16 rows x 32 k) of one 16-row tile from a stage.
-template <bool KC>
-__device__ __forceinline__ void frag(Frag<bf16_t>& f, const uint8_t* st, const FragOff<KC>& fo) {
-  if constexpr (KC) {
-    f.v = *reinterpret_cast<const uint4*>(st + fo.o[0]);
-  } else {
-    const uint2 lo = ds_read_tr8(st + fo.o[0]), hi = ds_read_tr8(st + fo.o[1]);
-    f.v = make_uint4(lo.x, lo.y, hi.x, hi.y);
-  }
-}
-
-// Wait until at most n of this thread's loads are outstanding (n even, <= 4).
-__device__ __forceinline__ void wait_loads(int n) {
-  if (n >= 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  else if (n >= 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
-
-}  // namespace p3
-
-template <bool AKC, bool BKC, int EPI>
-__global__ void __launch_bounds__(p3::NT) gemm_p3_kernel(GemmArgs g) {
-  using namespace p3;
-  __shared__ __attribute__((aligned(1024))) uint8_t sa0[OPB], sa1[OPB], sa2[OPB], sa3[OPB];
-  __shared__ __attribute__((aligned(1024))) uint8_t sb0[OPB], sb1[OPB], sb2[OPB], sb3[OPB];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int wm = w / WN, wn = w % WN;
-
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const int total = tiles_m * tiles_n;
-  int pid = blockIdx.x;
-  if ((total & 7) == 0) pid = (pid & 7) * (total >> 3) + (pid >> 3);
-  constexpr int GROUP = 8;
-  const int per_group = GROUP * tiles_n;
-  const int first_m = (pid / per_group) * GROUP;
-  const int gsize = min(tiles_m - first_m, GROUP);
-  const int pid_m = first_m + (pid % per_group) % gsize;
-  const int pid_n = (pid % per_group) / gsize;
-  const int m0 = pid_m * BM, n0 = pid_n * BN;
-
-  Src<AKC> sra;
-  Src<BKC> srb;
-  sra.init(static_cast<const bf16_t*>(g.A), g.lda, m0, g.M, tid);
-  srb.init(static_cast<const bf16_t*>(g.B), g.ldb, n0, g.N, tid);
-  const int nk = g.K / BK;
-
-  f32x4_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  FragOff<AKC> foa[TM];
-  FragOff<BKC> fob[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) foa[i].init(wm * TM * 16 + i * 16, lane);
-#pragma unroll
-  for (int j = 0; j < TN; ++j) fob[j].init(wn * TN * 16 + j * 16, lane);
-
-  auto stage_a = [&](int s) -> uint8_t* { return s == 0 ? sa0 : s == 1 ? sa1 : s == 2 ? sa2 : sa3; };
-  auto stage_b = [&](int s) -> uint8_t* { return s == 0 ? sb0 : s == 1 ? sb1 : s == 2 ? sb2 : sb3; };
-
-  // prologue: tiles 0, 1, 2
-#pragma unroll
-  for (int s = 0; s < 3; ++s)
-    if (s < nk) {
-      sra.load(stage_a(s), s, w);
-      srb.load(stage_b(s), s, w);
-    }
-
-  auto body = [&](auto S_, int t) {
-    constexpr int S = decltype(S_)::value;
-    // loads issued for tiles t+1 .. min(t+2, nk-1) may stay in flight
-    wait_loads(2 * (min(t + 2, nk - 1) - t));
-    barrier_only();
-    if (t + 3 < nk) {
-      sra.load(stage_a((S + 3) & 3), t + 3, w);
-      srb.load(stage_b((S + 3) & 3), t + 3, w);
-    }
-    const uint8_t* as = stage_a(S);
-    const uint8_t* bs = stage_b(S);
-    Frag<bf16_t> fa[TM], fb[TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) frag<AKC>(fa[i], as, foa[i]);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) frag<BKC>(fb[j], bs, fob[j]);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) mfma16(acc[i][j], fb[j], fa[i]);
-  };
-  // four stages per loop iteration, so every stage index is a constant
-  for (int t = 0; t < nk; t += 4 * P3_ROUNDS) {
-#pragma unroll
-    for (int r = 0; r < P3_ROUNDS; ++r) {
-      const int tr = t + 4 * r;
-      if (tr < nk) body(std::integral_constant<int, 0>{}, tr);
-      if (tr + 1 < nk) body(std::integral_constant<int, 1>{}, tr + 1);
-      if (tr + 2 < nk) body(std::integral_constant<int, 2>{}, tr + 2);
-      if (tr + 3 < nk) body(std::integral_constant<int, 3>{}, tr + 3);
-    }
-  }
-
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every direct load has landed
-  // acc[i][j][r] = C[m][nb + r]
-  const bool ld_vec = (g.ldc & 3) == 0;
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = m0 + (wm * TM + i) * 16 + lr;
-    if (m >= g.M) continue;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int nb = n0 + (wn * TN + j) * 16 + lg * 4;
-      if (nb >= g.N) continue;
-      float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-      epilogue4<bf16_t, EPI>(g, m, nb, v, ld_vec);
-    }
-  }
-}
-
-
-// Four-wave variant of the pipelined kernel: the same 256x256 tile, k tile
-// and LDS layouts, but four waves of 128x128 (one per SIMD, accumulators in
-// AGPRs) whose fragment registers are double-buffered, so that the LDS reads
-// of tile t+1 are issued between the MFMAs of tile t instead of after a
-// barrier that every wave of the CU has to reach first.  A stage is free once
-// the barrier that follows the reads of its tile has passed; the loads of
-// tile t+4 go into the stage of tile t, so four tiles are in flight.
-#ifndef ATOM_GEMM_P4
-#define ATOM_GEMM_P4 1
-#endif
-namespace p4 {
-constexpr int BM = 256, BN = 256, BK = 32, WM = 2, WN = 2, NT = 64 * WM * WN;
-constexpr int TM = BM / (16 * WM), TN = BN / (16 * WN);
-constexpr int OPB = BM * BK * 2;
-constexpr int LPT = OPB / (NT * 16);  // direct loads per thread per operand and tile
-
-// Barrier after this wave's LDS reads have completed; the wait is the
-// builtin so that the compiler knows those fragment registers are ready.
-__device__ __forceinline__ void barrier_after_reads() {
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), vmcnt and expcnt unconstrained
-  asm volatile("s_barrier" ::: "memory");
-}
-
-// acc += a b with the accumulator pinned to its AGPRs.  The 256 accumulator
-// registers of a wave fill the AGPR file; left to itself the register
-// allocator splits them between AGPRs and VGPRs and copies them around every
-// MFMA.  Issued in program order (volatile); the kernel supplies the wait
-// states between the accumulators' other writes and reads and these MFMAs.
-__device__ __forceinline__ void mfma_agpr(f32x4_t& acc, const Frag<bf16_t>& a, const Frag<bf16_t>& b) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-               : "+a"(acc)
-               : "v"(__builtin_bit_cast(bf16x8_t, a.v)), "v"(__builtin_bit_cast(bf16x8_t, b.v)));
-}
-}  // namespace p4
-
-template <bool AKC, bool BKC, int EPI>
-__global__ void __launch_bounds__(p4::NT) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_p4_kernel(GemmArgs g) {
-  using namespace p4;
-  using p3::Src;
-  using p3::FragOff;
-  // stages 0..3 of A, then of B; after the loop, the epilogue's staging
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[8 * OPB];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int wm = w / WN, wn = w % WN;
-
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const int total = tiles_m * tiles_n;
-  int pid = blockIdx.x;
-  if ((total & 7) == 0) pid = (pid & 7) * (total >> 3) + (pid >> 3);
-  constexpr int GROUP = 8;
-  const int per_group = GROUP * tiles_n;
-  const int first_m = (pid / per_group) * GROUP;
-  const int gsize = min(tiles_m - first_m, GROUP);
-  const int pid_m = first_m + (pid % per_group) % gsize;
-  const int pid_n = (pid % per_group) / gsize;
-  const int m0 = pid_m * BM, n0 = pid_n * BN;
-
-  // load q of a thread is the 16-byte chunk q * NT + tid of the tile
-  Src<AKC> sra[LPT];
-  Src<BKC> srb[LPT];
-#pragma unroll
-  for (int q = 0; q < LPT; ++q) {
-    sra[q].init(static_cast<const bf16_t*>(g.A), g.lda, m0, g.M, q * NT + tid);
-    srb[q].init(static_cast<const bf16_t*>(g.B), g.ldb, n0, g.N, q * NT + tid);
-  }
-  // k range of this workgroup: split blockIdx.y of gridDim.y equal ranges
-  // (the launcher makes each a multiple of four k tiles)
-  const int nk = g.K / BK / static_cast<int>(gridDim.y);
-  const int kbase = static_cast<int>(blockIdx.y) * nk;
-  // Each XCD starts its k loop at its own eighth of the range (the tile's
-  // sum is rotated, the same for every launch of the shape).  Workgroups
-  // walk k in step, so without it the whole GPU reads the same column range
-  // of every row at once; when both operands are k-contiguous, rows of a long
-  // k are 32 KB apart and those addresses share their low bits, which crowds
-  // a few memory channels (4096x4096x16384: 500 -> 418 us).  The workgroups
-  // of one XCD share operand tiles through its L2, so they keep one offset.
-  const int koff = ((total & 7) == 0) ? ((blockIdx.x & 7) * (nk >> 3)) & ~3 : 0;
-  auto rot = [&](int kt) {
-    const int r = kt + koff;
-    return kbase + (r >= nk ? r - nk : r);
-  };
-
-  f32x4_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      asm volatile("" : "+a"(acc[i][j]));
-    }
-  // wait states between the zeroing writes and the first MFMA reading them
-  asm volatile("s_nop 7\n\ts_nop 7");
-
-  FragOff<AKC> foa[TM];
-  FragOff<BKC> fob[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) foa[i].init(wm * TM * 16 + i * 16, lane);
-#pragma unroll
-  for (int j = 0; j < TN; ++j) fob[j].init(wn * TN * 16 + j * 16, lane);
-
-  auto stage_a = [&](int s) -> uint8_t* { return lds + s * OPB; };
-  auto stage_b = [&](int s) -> uint8_t* { return lds + (4 + s) * OPB; };
-  auto load_tile = [&](int s, int kt) {
-#pragma unroll
-    for (int q = 0; q < LPT; ++q) sra[q].load(stage_a(s), kt, q * (NT / 64) + w);
-#pragma unroll
-    for (int q = 0; q < LPT; ++q) srb[q].load(stage_b(s), kt, q * (NT / 64) + w);
-  };
-
-  Frag<bf16_t> fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-  // prologue: tiles 0..3 in flight, fragments of tile 0 in set 0.  Loads
-  // past the last tile repeat it (into stages nobody reads again), so every
-  // iteration has the same loads outstanding; they land before the exit.
-#pragma unroll
-  for (int s = 0; s < 4; ++s) load_tile(s, rot(min(s, nk - 1)));
-  asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
-  barrier_after_reads();
-#pragma unroll
-  for (int i = 0; i < TM; ++i) p3::frag<AKC>(fa0[i], stage_a(0), foa[i]);
-#pragma unroll
-  for (int j = 0; j < TN; ++j) p3::frag<BKC>(fb0[j], stage_b(0), fob[j]);
-
-  auto body = [&](auto S_, int t, Frag<bf16_t>(&ca)[TM], Frag<bf16_t>(&cb)[TN], Frag<bf16_t>(&na)[TM],
-                  Frag<bf16_t>(&nb)[TN]) {
-    constexpr int S = decltype(S_)::value;
-    // tile t+1 has landed for every wave, and every wave has read tile t
-    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-    barrier_after_reads();
-    const int kt = rot(min(t + 4, nk - 1));
-    // per row i: the fragments i of tile t+1 (after the last tile they come
-    // from a stale stage and are never used), then the MFMAs of row i of this
-    // tile, which hide the reads' latency, with one direct load of tile t+4
-    // half way (3-4 % faster than at the row's start; clustering the loads
-    // cost 3-5 %)
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      p3::frag<AKC>(na[i], stage_a((S + 1) & 3), foa[i]);
-      p3::frag<BKC>(nb[i], stage_b((S + 1) & 3), fob[i]);
-#pragma unroll
-      for (int j = 0; j < TN / 2; ++j) mfma_agpr(acc[i][j], cb[j], ca[i]);
-      if (i < LPT) sra[i].load(stage_a(S), kt, i * (NT / 64) + w);
-      else if (i < 2 * LPT) srb[i - LPT].load(stage_b(S), kt, (i - LPT) * (NT / 64) + w);
-#pragma unroll
-      for (int j = TN / 2; j < TN; ++j) mfma_agpr(acc[i][j], cb[j], ca[i]);
-    }
-  };
-  // nk is a multiple of 4: no tile is conditional inside the loop
-  for (int t = 0; t < nk; t += 4) {
-    body(std::integral_constant<int, 0>{}, t, fa0, fb0, fa1, fb1);
-    body(std::integral_constant<int, 1>{}, t + 1, fa1, fb1, fa0, fb0);
-    body(std::integral_constant<int, 2>{}, t + 2, fa0, fb0, fa1, fb1);
-    body(std::integral_constant<int, 3>{}, t + 3, fa1, fb1, fa0, fb0);
-  }
-
-  // every direct load has landed; wait states between the last MFMAs and
-  // the reads of their accumulators
-  asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
-  // Epilogue through LDS, 32 rows of the wave's 128x128 block at a time: the
-  // accumulators go to a wave-private [32][128] fp32 staging area, and each
-  // lane takes back 4 consecutive columns of one row, so a wave's stores (and
-  // the epilogue's reads of bias, residual or saved pre-activations) cover
-  // two whole 128-column rows instead of 32-byte pieces of 16 rows.
-  barrier_after_reads();  // every wave is done with the stages
-  constexpr int PITCH = 132;  // floats per staged row; rows 16 bytes of banks apart
-  float* stg = reinterpret_cast<float*>(lds) + w * (32 * PITCH);
-  const int row0 = m0 + wm * TM * 16, col0 = n0 + wn * TN * 16;
-  // N, ldc and ldaux are multiples of 4 (p4_applies): a lane's four columns
-  // are all inside the matrix or all past it, and every access is one
-  // 4-vector.  They are the same columns in every row the lane stores, so the
-  // bias is loaded once and the row pointers advance by a fixed stride.
-  const int cc = 4 * (lane & 31), nb = col0 + cc, rsub = lane >> 5;
-  const bool col_ok = nb < g.N;
-  float bv[4] = {0.f, 0.f, 0.f, 0.f};
-  if constexpr (epi_has_bias<EPI>())
-    if (col_ok) {
-      const uint2 w2 = *reinterpret_cast<const uint2*>(static_cast<const bf16_t*>(g.bias) + nb);
-      bv[0] = bf2f(w2.x & 0xffff); bv[1] = bf2f(w2.x >> 16); bv[2] = bf2f(w2.y & 0xffff); bv[3] = bf2f(w2.y >> 16);
-    }
-  // The element operands (C itself, the fp32 residual or the saved bf16
-  // pre-activation) are requested ahead of their use: every CU reaches its
-  // epilogue at about the same time, so a load issued just before its use
-  // waits out a GPU-wide burst.  bf16 operands go out two blocks of 32 rows
-  // ahead (two registers per row), fp32 ones one block ahead.
-  // Interior blocks take a branch-free copy of the epilogue: with per-row
-  // bounds tests the compiler waits for every load in flight at each test,
-  // which defeats the loads issued ahead.
-  auto epilogue = [&](auto GUARD_, auto EPI_, const GemmArgs& ga) {
-    constexpr bool GUARD = decltype(GUARD_)::value;
-    constexpr int E = decltype(EPI_)::value;
-    constexpr bool F32_OUT = E == EPI_STORE_F32 || E == EPI_ACC_F32 || E == EPI_BIAS_RESID;
-    constexpr bool ELEM = epi_reads_elem<E>();
-    constexpr int AHEAD = E == EPI_GELU_BWD ? 2 : 1;
-    using Raw = typename std::conditional<E == EPI_GELU_BWD, uint2, float4>::type;
-    Raw xr[TM / 2][16];
-    auto load_block = [&](int h) {
-      const int mq = row0 + h * 32 + rsub;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        if (!GUARD || (mq + 2 * q < ga.M && col_ok)) {
-          if constexpr (E == EPI_GELU_BWD)
-            xr[h][q] = *reinterpret_cast<const uint2*>(static_cast<const bf16_t*>(ga.aux) +
-                                                       static_cast<int64_t>(mq + 2 * q) * ga.ldaux + nb);
-          else
-            xr[h][q] = *reinterpret_cast<const float4*>((E == EPI_ACC_F32 ? static_cast<const float*>(ga.C) : ga.resid) +
-                                                        static_cast<int64_t>(mq + 2 * q) * ga.ldc + nb);
-        }
-      }
-    };
-    if constexpr (ELEM) {
-#pragma unroll
-      for (int h = 0; h <= AHEAD; ++h) load_block(h);
-    }
-#pragma unroll
-    for (int h = 0; h < TM / 2; ++h) {
-      if constexpr (ELEM)
-        if (h > 0 && h + AHEAD < TM / 2) load_block(h + AHEAD);
-      const int mq = row0 + h * 32 + rsub;  // row of q = 0; row q is mq + 2q
-      const int64_t cq = static_cast<int64_t>(mq) * ga.ldc + nb, aq = static_cast<int64_t>(mq) * ga.ldaux + nb;
-#pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const f32x4_t& a = acc[2 * h + ii][j];
-          *reinterpret_cast<float4*>(stg + (ii * 16 + lr) * PITCH + j * 16 + lg * 4) = make_float4(a[0], a[1], a[2], a[3]);
-        }
-      float4 sv[16];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) sv[q] = *reinterpret_cast<const float4*>(stg + (2 * q + rsub) * PITCH + cc);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        if (GUARD && !(mq + 2 * q < ga.M && col_ok)) continue;
-        float v[4] = {sv[q].x, sv[q].y, sv[q].z, sv[q].w};
-        const int64_t off = cq + 2 * q * ga.ldc;
-        float xe[4] = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (E == EPI_GELU_BWD) {
-          xe[0] = bf2f(xr[h][q].x & 0xffff); xe[1] = bf2f(xr[h][q].x >> 16);
-          xe[2] = bf2f(xr[h][q].y & 0xffff); xe[3] = bf2f(xr[h][q].y >> 16);
-        } else if constexpr (ELEM) {
-          xe[0] = xr[h][q].x; xe[1] = xr[h][q].y; xe[2] = xr[h][q].z; xe[3] = xr[h][q].w;
-        }
-        // the arithmetic of epilogue4, in the same order
-        if constexpr (E == EPI_ACC_F32) {
-          for (int r = 0; r < 4; ++r) v[r] += xe[r];
-        } else if constexpr (E == EPI_BIAS) {
-          for (int r = 0; r < 4; ++r) v[r] += bv[r];
-        } else if constexpr (E == EPI_BIAS_GELU) {
-          float gv[4];
-          for (int r = 0; r < 4; ++r) {
-            const float u = to_f<bf16_t>(from_f<bf16_t>(v[r] + bv[r]));
-            v[r] = u;
-            gv[r] = gelu_f(u);
-          }
-          *reinterpret_cast<uint2*>(static_cast<bf16_t*>(ga.aux) + aq + 2 * q * ga.ldaux) =
-              make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
-          for (int r = 0; r < 4; ++r) v[r] = gv[r];
-        } else if constexpr (E == EPI_BIAS_RESID) {
-          for (int r = 0; r < 4; ++r) v[r] = xe[r] + (v[r] + bv[r]);
-        } else if constexpr (E == EPI_GELU_BWD) {
-          for (int r = 0; r < 4; ++r) v[r] *= gelu_grad_f(xe[r]);
-        }
-        if constexpr (F32_OUT)
-          *reinterpret_cast<float4*>(static_cast<float*>(ga.C) + off) = make_float4(v[0], v[1], v[2], v[3]);
-        else
-          *reinterpret_cast<uint2*>(static_cast<bf16_t*>(ga.C) + off) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
-      }
-    }
-  };
-  const bool interior = row0 + TM * 16 <= g.M && col0 + TN * 16 <= g.N;
-  if constexpr (EPI == EPI_STORE || EPI == EPI_STORE_F32 || EPI == EPI_ACC_F32) {
-    if (gridDim.y > 1) {
-      // a split over k: the raw fp32 sums go to ws[split][M][N], and
-      // splitk_reduce adds the splits in order and applies the epilogue
-      GemmArgs gw = g;
-      gw.C = g.ws + static_cast<int64_t>(blockIdx.y) * g.M * g.N;
-      gw.ldc = g.N;
-      if (interior) epilogue(std::false_type{}, std::integral_constant<int, EPI_STORE_F32>{}, gw);
-      else epilogue(std::true_type{}, std::integral_constant<int, EPI_STORE_F32>{}, gw);
-      return;
-    }
-  }
-  if (interior) epilogue(std::false_type{}, std::integral_constant<int, EPI>{}, g);
-  else epilogue(std::true_type{}, std::integral_constant<int, EPI>{}, g);
-}
-
-
-// The pipelined kernels apply to bf16 problems with k a multiple of 32 and
-// (for clamped edge rows) M and N multiples of 8 with 16-byte aligned rows;
-// launch_p3 takes those with at least one 256x256 tile per CU.
-bool pipe_shape_ok(const GemmArgs& g) {
-  return ATOM_GEMM_PIPE && g.K % p3::BK == 0 && g.K > 0 && g.M % 8 == 0 && g.N % 8 == 0 && g.lda % 8 == 0 &&
-         g.ldb % 8 == 0 && g.M >= 8 && g.N >= 8;
-}
-
-int pipe_tiles(const GemmArgs& g) { return ((g.M + p3::BM - 1) / p3::BM) * ((g.N + p3::BN - 1) / p3::BN); }
-
-bool p3_applies(const GemmArgs& g) { return pipe_shape_ok(g) && pipe_tiles(g) >= 256; }
-
-// The four-wave kernel takes every epilogue when k is a multiple of four k
-// tiles and the output rows (and the saved pre-activation's) are 16-byte
-// aligned.
-bool p4_applies(const GemmArgs& g, int epi) {
+// The direct-load kernel (gemm_dl.h) takes problems whose 16-byte chunks are
+// whole: k, leading dimensions and the row count of an operand that is not
+// k-contiguous multiples of a chunk, and output rows (and the saved
+// pre-activation's) of whole 4-vectors.
+bool dl_applies(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
+  const int e = 16 / esz;
   const bool aux = epi == EPI_BIAS_GELU || epi == EPI_GELU_BWD;
-  return ATOM_GEMM_P4 && g.K % (4 * p4::BK) == 0 && g.ldc % 4 == 0 && (!aux || g.ldaux % 4 == 0);
+  return g.K > 0 && g.K % e == 0 && g.lda % e == 0 && g.ldb % e == 0 && (akc || g.M % e == 0) && (bkc || g.N % e == 0) &&
+         g.N % 4 == 0 && g.ldc % 4 == 0 && (!aux || g.ldaux % 4 == 0);
 }
 
-template <bool AKC, bool BKC>
-hipError_t launch_p3(const GemmArgs& g, int epi, hipStream_t s) {
-  const int tiles = ((g.M + p3::BM - 1) / p3::BM) * ((g.N + p3::BN - 1) / p3::BN);
-  const bool four = p4_applies(g, epi);
-  const dim3 grid(tiles);
-  switch (epi) {
-#define ATOM_CASE4(E)                                                                             \
-  case E:                                                                                         \
-    if (four) hipLaunchKernelGGL((gemm_p4_kernel<AKC, BKC, E>), grid, dim3(p4::NT), 0, s, g);      \
-    else hipLaunchKernelGGL((gemm_p3_kernel<AKC, BKC, E>), grid, dim3(p3::NT), 0, s, g);           \
-    break;
-#define ATOM_CASE3(E) \
-  case E: hipLaunchKernelGGL((gemm_p3_kernel<AKC, BKC, E>), grid, dim3(p3::NT), 0, s, g); break;
-    ATOM_CASE4(EPI_STORE)
-    ATOM_CASE4(EPI_STORE_F32)
-    ATOM_CASE4(EPI_ACC_F32)
-    ATOM_CASE4(EPI_BIAS)
-    ATOM_CASE4(EPI_BIAS_GELU)
-    ATOM_CASE4(EPI_BIAS_RESID)
-    ATOM_CASE4(EPI_GELU_BWD)
-#undef ATOM_CASE4
-#undef ATOM_CASE3
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+// Tile configurations of the direct-load kernel with the times the choice
+// rests on, in us: a CU's time for one k tile (32) of one workgroup, and for
+// a workgroup's start and epilogue.  Fitted to 963 problems (the four
+// configurations' layers, short and ragged token counts, vocabularies) x
+// every tile and split that fits, on one machine, for the smallest loss
+// against the best of them: 1.6 % on average.  What they say: big tiles read
+// the least per FLOP, 192 or 128 columns where 256 divide N badly
+// (16384x768x3072: 78 -> 75 us; 2048x5120x15360: 310 -> 273; 1000x8192x2048:
+// 54 -> 40), 128x128 and 64x64 where there are too few big tiles for 256 CUs
+// (1000x2048x8192: 157 -> 61, 44 split in two; 520x768x3072: 65 -> 17).
+struct TileCfg {
+  int bm, bn, occ;  // occ: workgroups a CU holds
+  double ktile, fixed;
+};
+constexpr TileCfg BF16_TILES[] = {
+    {256, 256, 1, 0.745, 7.2}, {256, 192, 1, 0.607, 5.5}, {256, 128, 1, 0.451, 4.2}, {128, 128, 2, 0.279, 0.43}, {64, 64, 4, 0.142, 0.0}};
+// fp32: the matrix cores bound both (512 and 128 MFMAs of 32 cycles per k
+// tile); 64x64 is 5-10 % faster where it fills the chip.
+constexpr TileCfg F32_TILES[] = {{64, 64, 2, 0.60, 0.5}, {32, 32, 4, 0.165, 0.1}};
+// A split over k: the second kernel's launch, and every partial written and
+// read once.
+constexpr double SPLIT_FIXED = 3.9, SPLIT_US_PER_PARTIAL = 1.34e-6;
+constexpr int MAX_SPLITS = 12;
+
+struct Choice {
+  int bm, bn, splits;
+};
+
+// The configuration and split count with the smallest predicted time.
+Choice choose(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
+  constexpr int CUS = 256;
+  const int quads = (g.K + 127) / 128;
+  const double mn = static_cast<double>(g.M) * g.N;
+  Choice best{0, 0, 1};
+  double best_t = 0.0;
+  auto consider = [&](const TileCfg& c) {
+    if (c.bm == 256 && c.bn < 256 && !gemm_main_combo(akc, bkc, epi)) return;
+    const int64_t tiles = static_cast<int64_t>((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
+    for (int want = 1; want <= MAX_SPLITS; ++want) {
+      const int per = (quads + want - 1) / want, splits = (quads + per - 1) / per;
+      if (splits != want) continue;
+      // two groups of 128 k per range at least, and no more ranges than fill the chip twice
+      if (want > 1 && (per < 2 || tiles * want > 2 * CUS * c.occ || !g.ws || mn * want * 4 > static_cast<double>(g.ws_bytes)))
+        break;
+      // the most workgroups a CU gets
+      const double share = static_cast<double>((tiles * want + CUS - 1) / CUS);
+      double t = share * (4.0 * per * c.ktile + c.fixed);
+      if (want > 1) t += SPLIT_FIXED + SPLIT_US_PER_PARTIAL * mn * want;
+      if (best.bm == 0 || t < best_t) {
+        best = Choice{c.bm, c.bn, want};
+        best_t = t;
+      }
+    }
+  };
+  if (esz == 2) for (const auto& c : BF16_TILES) consider(c);
+  else for (const auto& c : F32_TILES) consider(c);
+  return best;
 }
 
-// The four-wave kernel on fewer 256x256 tiles than CUs (weight gradients of
-// the narrower layers): the split count over k, 1 from 192 tiles on, else the
-// smallest power of two that brings the workgroups to 192 or more, or the
-// largest one the workspace holds if that leaves at least 96; splits need an
-// epilogue that can follow their sum and k ranges of whole four-tile steps.
-// 0 where the kernel does not apply.
-int p4_splits(const GemmArgs& g, int epi, int tiles) {
-  if (!pipe_shape_ok(g) || !p4_applies(g, epi)) return 0;
-  if (tiles >= 192) return 1;
-  if (!(epi == EPI_STORE || epi == EPI_STORE_F32 || epi == EPI_ACC_F32) || !g.ws) return 0;
-  int best = 0;
-  for (int sp = 2; sp <= 16 && tiles * best < 192; sp *= 2) {
-    if (g.K % (4 * p4::BK * sp) != 0 || static_cast<uint64_t>(sp) * g.M * g.N * 4 > g.ws_bytes) break;
-    best = sp;
+template <typename T>
+hipError_t launch_dl(GemmArgs g, bool akc, bool bkc, int epi, hipStream_t s) {
+  const Choice c = choose(g, sizeof(T), akc, bkc, epi);
+  const int quads = (g.K + 127) / 128;
+  g.kquads = (quads + c.splits - 1) / c.splits;
+  g.splits = (quads + g.kquads - 1) / g.kquads;  // none empty
+  GemmArgs k = g;
+  const int kepi = g.splits > 1 ? EPI_STORE_F32 : epi;
+  if (g.splits > 1) {
+    k.C = g.ws;
+    k.ldc = g.N;
   }
-  return tiles * best >= 96 ? best : 0;
+  hipError_t e;
+  if constexpr (sizeof(T) == 4)
+    e = c.bm == 64 ? gemm_dl_f32_64(k, akc, bkc, kepi, s) : gemm_dl_f32_32(k, akc, bkc, kepi, s);
+  else
+    e = c.bm == 64    ? gemm_dl_64(k, akc, bkc, kepi, s)
+        : c.bm == 128 ? gemm_dl_128(k, akc, bkc, kepi, s)
+        : c.bn == 128 ? gemm_dl_256x128(k, akc, bkc, kepi, s)
+        : c.bn == 192 ? gemm_dl_192(k, akc, bkc, kepi, s)
+                      : gemm_dl_256(k, akc, bkc, kepi, s);
+  if (e != hipSuccess || g.splits == 1) return e;
+  return launch_reduce<T>(g, epi, g.splits, s);
 }
 
-template <bool AKC, bool BKC>
-hipError_t launch_p4_split(const GemmArgs& g, int epi, int tiles, int splits, hipStream_t s) {
-  const dim3 grid(tiles, splits);
-  switch (epi) {
-#define ATOM_CASE(E) \
-  case E: hipLaunchKernelGGL((gemm_p4_kernel<AKC, BKC, E>), grid, dim3(p4::NT), 0, s, g); break;
-    ATOM_CASE(EPI_STORE)
-    ATOM_CASE(EPI_STORE_F32)
-    ATOM_CASE(EPI_ACC_F32)
-    ATOM_CASE(EPI_BIAS)
-    ATOM_CASE(EPI_BIAS_GELU)
-    ATOM_CASE(EPI_BIAS_RESID)
-    ATOM_CASE(EPI_GELU_BWD)
-#undef ATOM_CASE
-    default: return hipErrorInvalidValue;
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || splits == 1) return e;
-  const int64_t MN = static_cast<int64_t>(g.M) * g.N;
-  dim3 rgrid(static_cast<unsigned>((MN / 4 + 255) / 256 + 1)), rblock(256);
-  switch (epi) {
-    case EPI_STORE: hipLaunchKernelGGL((splitk_reduce<bf16_t, EPI_STORE>), rgrid, rblock, 0, s, g, splits); break;
-    case EPI_STORE_F32: hipLaunchKernelGGL((splitk_reduce<bf16_t, EPI_STORE_F32>), rgrid, rblock, 0, s, g, splits); break;
-    case EPI_ACC_F32: hipLaunchKernelGGL((splitk_reduce<bf16_t, EPI_ACC_F32>), rgrid, rblock, 0, s, g, splits); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-// Tile configuration and split count for a problem: the large tile when it
-// gives at least one workgroup per CU, else the 128x128 tile; a split over k
-// when even that leaves the CUs idle and k is long (weight gradients of
-// small layers), limited by the workspace.
+// Everything else: 128x128 tiles, split over k where those leave the CUs idle
+// and k is long, limited by the workspace.
 template <typename T, bool AKC, bool BKC>
 hipError_t launch_t(const GemmArgs& g, int epi, hipStream_t s) {
   constexpr int CUS = 256;
-  if constexpr (sizeof(T) == 2) {
-    if (p3_applies(g)) return launch_p3<AKC, BKC>(g, epi, s);
-    const int tiles = pipe_tiles(g), splits = p4_splits(g, epi, tiles);
-    if (splits > 0) return launch_p4_split<AKC, BKC>(g, epi, tiles, splits, s);
-  }
-  const int tiles_big = ((g.M + Big::BM - 1) / Big::BM) * ((g.N + Big::BN - 1) / Big::BN);
-  if (tiles_big >= CUS) return launch_cfg<T, AKC, BKC, Big>(g, epi, 1, s);
-  const int tiles = ((g.M + Small::BM - 1) / Small::BM) * ((g.N + Small::BN - 1) / Small::BN);
+  if (dl_applies(g, sizeof(T), AKC, BKC, epi)) return launch_dl<T>(g, AKC, BKC, epi, s);
+  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   const int nk = (g.K + Tile<T>::BK - 1) / Tile<T>::BK;
   int splits = 1;
-  const bool can_split = epi == EPI_STORE || epi == EPI_STORE_F32 || epi == EPI_ACC_F32;
-  if (can_split && g.ws && tiles < 2 * CUS && nk >= 32) {
+  if (g.ws && tiles < 2 * CUS && nk >= 32) {
     splits = std::min((2 * CUS + tiles - 1) / tiles, nk / 16);
     const int64_t per = static_cast<int64_t>(g.M) * g.N * 4;
     splits = static_cast<int>(std::min<int64_t>(splits, static_cast<int64_t>(g.ws_bytes / per)));
     splits = std::max(1, std::min(splits, 16));
   }
-  return launch_cfg<T, AKC, BKC, Small>(g, epi, splits, s);
+  return launch_small<T, AKC, BKC>(g, epi, splits, s);
 }
 
 }  // namespace

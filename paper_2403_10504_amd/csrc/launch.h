@@ -30,7 +30,26 @@ struct GemmArgs {
   int M, N, K;
   float* ws;          // optional fp32 workspace for a split over k (may be null)
   uint64_t ws_bytes;  // its size; a split needs splits * M * N * 4 bytes
+  int splits, kquads; // set by the launcher: k ranges and the groups of 128 k of each
 };
+
+// The layout and epilogue combinations of the training step: forward, data
+// gradient and weight gradient of a linear layer.
+constexpr bool gemm_main_combo(bool akc, bool bkc, int epi) {
+  if (akc && bkc) return epi != EPI_ACC_F32 && epi != EPI_GELU_BWD;
+  if (akc) return epi == EPI_STORE || epi == EPI_STORE_F32 || epi == EPI_GELU_BWD;
+  return !bkc && (epi == EPI_STORE || epi == EPI_STORE_F32 || epi == EPI_ACC_F32);
+}
+
+// Tile configurations of the direct-load kernel (gemm_dl.h); 256x192 and
+// 256x128 exist for gemm_main_combo only.
+hipError_t gemm_dl_256(const GemmArgs& g, bool akc, bool bkc, int epi, hipStream_t s);
+hipError_t gemm_dl_192(const GemmArgs& g, bool akc, bool bkc, int epi, hipStream_t s);
+hipError_t gemm_dl_256x128(const GemmArgs& g, bool akc, bool bkc, int epi, hipStream_t s);
+hipError_t gemm_dl_128(const GemmArgs& g, bool akc, bool bkc, int epi, hipStream_t s);
+hipError_t gemm_dl_64(const GemmArgs& g, bool akc, bool bkc, int epi, hipStream_t s);
+hipError_t gemm_dl_f32_64(const GemmArgs& g, bool akc, bool bkc, int epi, hipStream_t s);
+hipError_t gemm_dl_f32_32(const GemmArgs& g, bool akc, bool bkc, int epi, hipStream_t s);
 
 hipError_t gemm_check(const GemmArgs& g, int dtype, bool a_kcontig, bool b_kcontig);
 hipError_t gemm(const GemmArgs& g, int dtype, bool a_kcontig, bool b_kcontig, int epi, hipStream_t s);

@@ -208,6 +208,32 @@ def check_pipelined(akc, bkc, epi, M, N, K, seed, ws_bytes=0):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (65, 68, 40), (31, 36, 136), (129, 260, 264), (520, 392, 520)])
+def test_gemm_direct_load_edges(dtype, M, N, K):
+    """The direct-load kernel at the edges of its small tiles (64 and 128 rows in
+    bf16, 32 and 64 in fp32), with k ending inside a tile of 32 and inside a
+    group of 128 (the chunks past k read zeros), and row counts that only a
+    k-contiguous operand may have.  Tolerances as for test_gemm_layouts."""
+    for akc, bkc in ((1, 1), (1, 0), (0, 0), (0, 1)):
+        Mr, Nr = (M if akc else (M + 7) // 8 * 8), (N if bkc else (N + 7) // 8 * 8)
+        err, tol = gemm_case(dtype, akc, bkc, Mr, Nr, K, A.ATOM_EPI_STORE, seed=M + N + K + akc + 2 * bkc)
+        assert err < tol, (akc, bkc, err)
+
+
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0)])
+@pytest.mark.parametrize("M,N,K,ws", [
+    (4008, 3064, 520, 0),  # 256x192 tiles, ragged rows, k ends inside a group of 128
+    (1000, 8192, 2056, 0),  # 256x128 tiles, likewise
+    (136, 392, 8200, 64 << 20),  # splits of k, the last one short, before every epilogue
+])
+@pytest.mark.parametrize("epi", ALL_EPI)
+def test_gemm_direct_load_tiles(akc, bkc, M, N, K, ws, epi):
+    """Tile shapes and splits that the other sizes here do not reach; tolerances as
+    for the pipelined path (one bf16 rounding, or fp32 sums of exact products)."""
+    check_pipelined(akc, bkc, epi, M, N, K, seed=300 + akc + 2 * bkc + 4 * epi + K, ws_bytes=ws)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_gemm_split_k_is_exact_and_deterministic(dtype):
     M, N, K = 256, 392, 8192  # few output tiles, long k: splits over k
     ws = 16 * M * N * 4
