@@ -632,37 +632,6 @@ __global__ void __launch_bounds__(256) attn_delta_kernel(const T* __restrict__ o
   }
 }
 
-// bf16: eight consecutive elements per thread (16-byte loads), DH/8 threads
-// per (row, head) summed by shuffles in a fixed order.  Head h of row r sits
-// at (r*H + h)*DH, so the pairs are contiguous and a workgroup reads one
-// contiguous range of O and of dO.
-template <int DH>
-__global__ void __launch_bounds__(256) attn_delta_bf16_kernel(const bf16_t* __restrict__ o,
-                                                              const bf16_t* __restrict__ dout,
-                                                              float* __restrict__ delta, int64_t n_pairs, int Tn,
-                                                              int H) {
-  constexpr int G = DH / 8;
-  const int64_t gid = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int64_t idx = gid / G;
-  const int sub = static_cast<int>(gid % G);
-  float s = 0.f;
-  if (idx < n_pairs) {
-    const uint4 a = *reinterpret_cast<const uint4*>(o + idx * DH + 8 * sub);
-    const uint4 b = *reinterpret_cast<const uint4*>(dout + idx * DH + 8 * sub);
-    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      s += bf2f(aw[k] & 0xffff) * bf2f(bw[k] & 0xffff) + bf2f(aw[k] >> 16) * bf2f(bw[k] >> 16);
-  }
-#pragma unroll
-  for (int off = G / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (idx < n_pairs && sub == 0) {
-    const int64_t row = idx / H, bb = row / Tn, t = row % Tn;
-    const int h = static_cast<int>(idx % H);
-    delta[(bb * H + h) * Tn + t] = s;
-  }
-}
-
 // ------------------------------------------------------ backward: dK, dV
 template <typename T, int DH, int W>
 __global__ void __launch_bounds__(64 * W) attn_bwd_dkdv_kernel(const T* __restrict__ qkv,
@@ -1220,9 +1189,10 @@ __device__ __forceinline__ int dsw(int r) {
 
 template <int DH, int NW>
 __global__ void __launch_bounds__(64 * NW, DH == 64 ? 4 : 2) attn_bwd_dq_dl_kernel(const bf16_t* __restrict__ qkv,
+                                                                const bf16_t* __restrict__ o,
                                                                 const bf16_t* __restrict__ dout,
                                                                 const float* __restrict__ lse,
-                                                                const float* __restrict__ delta,
+                                                                float* __restrict__ delta,
                                                                 bf16_t* __restrict__ dqkv, int B, int Tn, int H) {
   using F = FwdDL<DH>;
   constexpr int NS = DH / 32, NCT = DH / 16, BQ = NW * 16, NT = 64 * NW, RB = DH * 2;
@@ -1251,7 +1221,6 @@ __global__ void __launch_bounds__(64 * NW, DH == 64 ? 4 : 2) attn_bwd_dq_dl_kern
 
   Frag<bf16_t> qf[NS], of[NS];
   const float lse_i = qi < Tn ? lse[(static_cast<int64_t>(b) * H + h) * Tn + qi] * LOG2E : INFINITY;
-  const float del_i = qi < Tn ? delta[(static_cast<int64_t>(b) * H + h) * Tn + qi] : 0.f;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     frag_global(qf[s], qb, ld, qi, Tn, 32 * s + 8 * lg);
@@ -1292,6 +1261,25 @@ __global__ void __launch_bounds__(64 * NW, DH == 64 ? 4 : 2) attn_bwd_dq_dl_kern
       if (kt + u < n_kt) load_tile(st * SUB + u, (kt + u) * BT);
   };
   load_stage(0, 0);
+  // D = rowsum(dO * O) of this lane's query: the lane's elements, then its
+  // four lane rows; kept for the dK/dV kernel, which runs after this one.
+  // (As a kernel of its own D read dO once more and cost a launch: 12.7 of
+  // 340 us of the backward at the 6.7B shape, 4 of 33 at three sequences of 333.)
+  float del_i = 0.f;
+  {
+    const bf16_t* orow = o + static_cast<int64_t>(b) * Tn * d + h * DH;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      Frag<bf16_t> f;
+      frag_global(f, orow, d, qi, Tn, 32 * s + 8 * lg);
+      const uint32_t a[4] = {f.v.x, f.v.y, f.v.z, f.v.w}, c[4] = {of[s].v.x, of[s].v.y, of[s].v.z, of[s].v.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        del_i += bf2f(a[k] & 0xffff) * bf2f(c[k] & 0xffff) + bf2f(a[k] >> 16) * bf2f(c[k] >> 16);
+    }
+    del_i = rows4_sum(del_i);
+    if (lg == 0 && qi < Tn) delta[(static_cast<int64_t>(b) * H + h) * Tn + qi] = del_i;
+  }
   for (int ks0 = 0; ks0 < n_kt; ks0 += SUB) {
     const int cur = (ks0 / SUB) & 1;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1409,35 +1397,31 @@ hipError_t fwd_t(const void* qkv, void* o, float* lse, int B, int Tn, int H, hip
 template <typename T, int DH>
 hipError_t bwd_t(const void* qkv, const void* o, const void* dout, const float* lse, float* delta, void* dqkv, int B,
                  int Tn, int H, hipStream_t s) {
-  constexpr int W = ACfg<T, DH>::W;
-  const int64_t n_rows = static_cast<int64_t>(B) * Tn;
-  if constexpr (sizeof(T) == 2)
-    hipLaunchKernelGGL(attn_delta_bf16_kernel<DH>, dim3(static_cast<unsigned>((n_rows * H * (DH / 8) + 255) / 256)),
-                       dim3(256), 0, s, static_cast<const bf16_t*>(o), static_cast<const bf16_t*>(dout), delta,
-                       n_rows * H, Tn, H);
-  else
-    hipLaunchKernelGGL(attn_delta_kernel<T>, dim3(static_cast<unsigned>((n_rows * H + 3) / 4)), dim3(256), 0, s,
-                       static_cast<const T*>(o), static_cast<const T*>(dout), delta, n_rows, Tn, H, DH);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if constexpr (sizeof(T) == 2)
+  constexpr int W = ACfg<T, DH>::W, GQ = ACfg<T, DH>::GQ, WQ = ACfg<T, DH>::WQ;
+  if constexpr (sizeof(T) == 2) {
+    // dQ first: it computes D
+    hipLaunchKernelGGL((attn_bwd_dq_dl_kernel<DH, WQ>), dim3((Tn + 16 * WQ - 1) / (16 * WQ), B * H), dim3(64 * WQ), 0,
+                       s, static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o),
+                       static_cast<const bf16_t*>(dout), lse, delta, static_cast<bf16_t*>(dqkv), B, Tn, H);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attn_bwd_dkdv_dl_kernel<DH, W>), dim3((Tn + 16 * W - 1) / (16 * W), B * H), dim3(64 * W), 0,
                        s, static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(dout), lse, delta,
                        static_cast<bf16_t*>(dqkv), B, Tn, H);
-  else
+  } else {
+    const int64_t n_rows = static_cast<int64_t>(B) * Tn;
+    hipLaunchKernelGGL(attn_delta_kernel<T>, dim3(static_cast<unsigned>((n_rows * H + 3) / 4)), dim3(256), 0, s,
+                       static_cast<const T*>(o), static_cast<const T*>(dout), delta, n_rows, Tn, H, DH);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<T, DH, W>), dim3((Tn + 16 * W - 1) / (16 * W), B * H), dim3(64 * W), 0,
                        s, static_cast<const T*>(qkv), static_cast<const T*>(dout), lse, delta, static_cast<T*>(dqkv),
                        B, Tn, H);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  constexpr int GQ = ACfg<T, DH>::GQ, WQ = ACfg<T, DH>::WQ;
-  if constexpr (sizeof(T) == 2)
-    hipLaunchKernelGGL((attn_bwd_dq_dl_kernel<DH, WQ>), dim3((Tn + 16 * WQ - 1) / (16 * WQ), B * H), dim3(64 * WQ), 0,
-                       s, static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(dout), lse, delta,
-                       static_cast<bf16_t*>(dqkv), B, Tn, H);
-  else
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL((attn_bwd_dq_kernel<T, DH, GQ, WQ>), dim3((Tn + 16 * WQ * GQ - 1) / (16 * WQ * GQ), B * H),
                        dim3(64 * WQ), 0, s, static_cast<const T*>(qkv), static_cast<const T*>(dout), lse, delta,
                        static_cast<T*>(dqkv), B, Tn, H);
+  }
   return hipGetLastError();
 }
 
