@@ -111,6 +111,10 @@ template <> struct Vec4<bf16_t> {
     o.y = pack_bf16(f[2], f[3]);
     *reinterpret_cast<uint2*>(p) = o;
   }
+  ATOM_DEV static void stream(bf16_t* p, const float* f) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    __builtin_nontemporal_store((u2{pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3])}), reinterpret_cast<u2*>(p));
+  }
 };
 template <> struct Vec4<float> {
   float4 v;
@@ -119,6 +123,7 @@ template <> struct Vec4<float> {
   ATOM_DEV static void store(float* p, const float* f) {
     *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
   }
+  ATOM_DEV static void stream(float* p, const float* f) { stream4(p, f); }
 };
 
 // Forward, one workgroup per row: four consecutive columns per thread and
@@ -609,7 +614,9 @@ __global__ void __launch_bounds__(256) xent_kernel(const float* __restrict__ z, 
 // each wave's shuffles then the 16 waves in a fixed order.  Columns V..lddz-1
 // of dz are zeroed; the loss row is lse - z[y] (NaN for y outside [0, V)).
 // Needs ldz and lddz multiples of 4 and 16-byte aligned rows (dispatch).
-template <typename T, int NV>
+// STREAM: logits that overflow the Infinity Cache are read, and dz written,
+// past the caches (2048 x 50304: 129 -> 117 us, 5.3 TB/s).
+template <typename T, int NV, bool STREAM>
 __global__ void __launch_bounds__(1024) xent_reg_kernel(const float* __restrict__ z, int64_t ldz,
                                                         const int32_t* __restrict__ tgt, T* __restrict__ dz,
                                                         int64_t lddz, float* __restrict__ loss_rows, int V,
@@ -625,7 +632,7 @@ __global__ void __launch_bounds__(1024) xent_reg_kernel(const float* __restrict_
   for (int i = 0; i < NV; ++i) {
     const int c = 4 * (tid + 1024 * i);
     if (c + 4 <= V) {
-      const float4 v = *reinterpret_cast<const float4*>(zr + c);
+      const float4 v = STREAM ? stream_load4(zr + c) : *reinterpret_cast<const float4*>(zr + c);
       x[i][0] = v.x;
       x[i][1] = v.y;
       x[i][2] = v.z;
@@ -668,7 +675,9 @@ __global__ void __launch_bounds__(1024) xent_reg_kernel(const float* __restrict_
     float g[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) g[e] = c + e < V ? (x[i][e] * inv - (c + e == y ? 1.f : 0.f)) * scale : 0.f;
-    Vec4<T>::store(dr + c, g);  // lddz is a multiple of 4: the chunk is inside the row
+    // lddz is a multiple of 4: the chunk is inside the row
+    if constexpr (STREAM) Vec4<T>::stream(dr + c, g);
+    else Vec4<T>::store(dr + c, g);
   }
   // a target outside [0, V) gives a NaN loss instead of an out-of-range read
   if (tid == 0) loss_rows[row] = (y >= 0 && y < V) ? m + logf(sum) - zr[y] : __builtin_nanf("");
@@ -956,14 +965,16 @@ hipError_t xent_fwd_bwd(int dtype, const float* logits, int64_t ldz, const int32
   if (ldz % 4 == 0 && lddz % 4 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0 &&
       reinterpret_cast<uintptr_t>(dz) % (4 * esz) == 0 && nv <= 16) {
     dim3 g1(static_cast<unsigned>(rows)), b1(1024);
-#define ATOM_XR(NV)                                                                                                 \
-  do {                                                                                                              \
-    if (dtype == DT_BF16)                                                                                           \
-      hipLaunchKernelGGL((xent_reg_kernel<bf16_t, NV>), g1, b1, 0, s, logits, ldz, tgt, static_cast<bf16_t*>(dz), \
-                         lddz, loss_rows, V, scale);                                                                \
-    else                                                                                                            \
-      hipLaunchKernelGGL((xent_reg_kernel<float, NV>), g1, b1, 0, s, logits, ldz, tgt, static_cast<float*>(dz),   \
-                         lddz, loss_rows, V, scale);                                                                \
+    const bool stream = rows * ldz * 4 > STREAM_BYTES;
+#define ATOM_XRS(T, NV, S)                                                                                        \
+  hipLaunchKernelGGL((xent_reg_kernel<T, NV, S>), g1, b1, 0, s, logits, ldz, tgt, static_cast<T*>(dz), lddz,       \
+                     loss_rows, V, scale)
+#define ATOM_XR(NV)                                                                                               \
+  do {                                                                                                            \
+    if (dtype == DT_BF16 && stream) ATOM_XRS(bf16_t, NV, true);                                                   \
+    else if (dtype == DT_BF16) ATOM_XRS(bf16_t, NV, false);                                                       \
+    else if (stream) ATOM_XRS(float, NV, true);                                                                   \
+    else ATOM_XRS(float, NV, false);                                                                              \
   } while (0)
     if (nv <= 1) ATOM_XR(1);
     else if (nv <= 2) ATOM_XR(2);
@@ -972,6 +983,7 @@ hipError_t xent_fwd_bwd(int dtype, const float* logits, int64_t ldz, const int32
     else if (nv <= 13) ATOM_XR(13);
     else ATOM_XR(16);
 #undef ATOM_XR
+#undef ATOM_XRS
     return hipGetLastError();
   }
   dim3 grid(static_cast<unsigned>(rows)), block(256);

@@ -361,6 +361,33 @@ def test_cross_entropy_rows(dtype, rows, V, ld):
     assert np.all(g[:, V:] == 0)
 
 
+def test_logits_larger_than_the_cache():
+    """fp32 logits of more than 256 MB (1400 x 50304 here) are stored, and read and
+    their gradient stored, past the caches: product and cross-entropy against the
+    oracle on sampled rows, and the gradient's padding columns."""
+    t = U.torch()
+    rows, V, ld, K = 1400, 50257, 50304, 72
+    g = t.Generator(device="cuda").manual_seed(9)
+    a = t.randn(rows, K, device="cuda", generator=g).to(t.bfloat16)
+    w = t.randn(ld, K, device="cuda", generator=g).to(t.bfloat16)
+    z = t.empty(rows, ld, device="cuda")
+    dz = t.full((rows, ld), 7.0, device="cuda", dtype=t.bfloat16)
+    y = t.randint(0, V, (rows,), device="cuda", generator=g, dtype=t.int32)
+    loss = t.empty(rows, device="cuda")
+    A.atom_k_gemm(A.ATOM_BF16, 1, 1, A.ATOM_EPI_STORE_F32, rows, ld, K, U.ptr(a), K, U.ptr(w), K, U.ptr(z), ld,
+                  stream=stream())
+    A.atom_k_xent(A.ATOM_BF16, U.ptr(z), ld, U.ptr(y), U.ptr(dz), ld, U.ptr(loss), rows, V, 0.5, stream())
+    U.sync()
+    pick = np.array([0, 1, 700, 1398, 1399])
+    zp = U.host(z[pick])
+    assert U.rel_err(zp, U.host(a[pick]) @ U.host(w).T) < 1e-4
+    loss_ref, dz_ref = gpt.cross_entropy_rows(zp[:, :V], y.cpu().numpy()[pick], 0.5)
+    assert U.rel_err(U.host(loss[pick]), loss_ref) < 1e-5
+    got = U.host(dz[pick])
+    assert U.rel_err(got[:, :V], dz_ref) < TOL_OUT["bf16"]
+    assert np.all(got[:, V:] == 0)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_colsum(dtype):
     r = U.rng(3)
