@@ -259,11 +259,16 @@ gemm_dl_kernel(GemmArgs g) {
   };
 
   f32x4_t acc[TM][TN];
+  // fp32: odd k tiles have accumulators of their own, so that a sum has half
+  // as many roundings in a row (k = 1024: 256 MFMAs of 4)
+  constexpr bool TWO = sizeof(T) == 4;
+  f32x4_t acc2[TWO ? TM : 1][TWO ? TN : 1];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if constexpr (TWO) acc2[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       if constexpr (PIN) asm volatile("" : "+a"(acc[i][j]));
     }
   // wait states between the zeroing writes and the first MFMA reading them
@@ -323,6 +328,7 @@ gemm_dl_kernel(GemmArgs g) {
             if (l * TM / LT == i) load(S, kt, l);
         }
         if constexpr (PIN) mfma_agpr(acc[i][j], cb[j], ca[i]);
+        else if constexpr (TWO && (S & 1)) mfma16(acc2[i][j], cb[j], ca[i]);
         else mfma16(acc[i][j], cb[j], ca[i]);
       }
     }
@@ -343,6 +349,12 @@ gemm_dl_kernel(GemmArgs g) {
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+  }
+  if constexpr (TWO) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] += acc2[i][j];
   }
   // Epilogue through LDS, RB rows of the wave's block at a time: the
   // accumulators go to a wave-private [RB][BN/2] fp32 staging area, and each
