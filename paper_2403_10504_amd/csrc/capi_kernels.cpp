@@ -60,9 +60,7 @@ int atom_k_layernorm_bwd(int dtype, const void* dy, const float* x, const float*
   int s = st(layernorm_bwd(dtype, dy, x, mean, rstd, gamma, dres, dres_lp, accumulate != 0, part, rows, d, S(stream)));
   if (s != ATOM_OK) return s;
   const int64_t np = layernorm_bwd_blocks(rows, d);
-  s = st(sum_parts(part, np, d, 2 * static_cast<int64_t>(d), DT_F32, dgamma, false, S(stream)));
-  if (s != ATOM_OK) return s;
-  return st(sum_parts(part + d, np, d, 2 * static_cast<int64_t>(d), DT_F32, dbeta, false, S(stream)));
+  return st(sum_parts2(part, np, 2 * d, 2 * static_cast<int64_t>(d), DT_F32, dgamma, dbeta, d, false, S(stream)));
 }
 
 int atom_k_attn_fwd(int dtype, const void* qkv, void* o, float* lse, int B, int T, int H, int dh, void* stream) {
@@ -80,9 +78,7 @@ int64_t atom_k_colsum_part_floats(int64_t rows, int cols) { return colsum_blocks
 
 int atom_k_colsum(int dtype, const void* x, int64_t rows, int cols, float* out, float* part, void* stream) {
   if (!dt_ok(dtype) || !x || !out || !part) return ATOM_EINVAL;
-  int s = st(colsum_partial(dtype, x, rows, cols, cols, part, S(stream)));
-  if (s != ATOM_OK) return s;
-  return st(sum_parts(part, colsum_blocks(rows), cols, cols, DT_F32, out, false, S(stream)));
+  return st(colsum(dtype, x, rows, cols, cols, part, DT_F32, out, false, S(stream)));
 }
 
 int atom_k_xent(int dtype, const float* logits, int64_t ldz, const int32_t* tgt, void* dz, int64_t lddz,

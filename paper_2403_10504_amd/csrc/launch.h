@@ -66,10 +66,13 @@ hipError_t layernorm_bwd(int dtype, const void* dy, const float* x, const float*
                          const void* gamma, float* dres, void* dres_lp, bool accumulate, float* part, int64_t rows,
                          int d, hipStream_t s);
 
-// Deterministic column sums of a [rows][cols] matrix in two passes.
+// Deterministic column sums of a [rows][cols] matrix, out[j] (op)= sum of
+// column j (out types and accumulate as for sum_parts): one launch for few
+// rows, else partials of 16 rows into part (colsum_blocks(rows) * cols floats)
+// and their sum.
 int64_t colsum_blocks(int64_t rows);
-hipError_t colsum_partial(int in_dtype, const void* x, int64_t rows, int cols, int64_t ld, float* part,
-                          hipStream_t s);
+hipError_t colsum(int in_dtype, const void* x, int64_t rows, int cols, int64_t ld, float* part, int out_dtype,
+                  void* out, bool accumulate, hipStream_t s);
 // out[j] (op)= sum over nparts of part[p][j] (+ stride between slabs); out
 // type: DT_F32 with accumulate flag, or the element type (overwrite).
 hipError_t sum_parts(const float* part, int64_t nparts, int cols, int64_t part_stride, int out_dtype, void* out,

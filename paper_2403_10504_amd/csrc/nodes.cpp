@@ -182,8 +182,7 @@ int block_forward(atom_ctx* c, int node, int micro, bool recompute) {
 
 // Bias gradient: column sums of x [N][cols] (dtype in_dt) into target.
 int bias_grad(atom_ctx* c, int in_dt, const void* x, int cols, float* part, const GradTarget& t) {
-  KCHK(c, colsum_partial(in_dt, x, c->N, cols, cols, part, c->cs));
-  KCHK(c, sum_parts(part, colsum_blocks(c->N), cols, cols, t.dtype, t.p, t.accumulate, c->cs));
+  KCHK(c, colsum(in_dt, x, c->N, cols, cols, part, t.dtype, t.p, t.accumulate, c->cs));
   return ATOM_OK;
 }
 

@@ -269,27 +269,30 @@ __global__ void __launch_bounds__(256) ln_bwd_wave_kernel(const T* __restrict__ 
   }
 }
 
-// Backward for d >= 1024: one workgroup (four waves) per block of LNT_ROWS
-// consecutive rows.  Thread t owns columns 4t + 1024j (j < NCH, 4-vector
+// Backward for d >= 1024: one workgroup of NT threads per block of LNT_ROWS
+// consecutive rows.  Thread t owns columns 4t + 4 NT j (j < NCH, 4-vector
 // loads), so each wave reads contiguous 512-byte (bf16) or 1 KB (fp32) runs;
 // every thread keeps gamma and its columns' running sums of dy*xhat and dy
 // in registers over the block's rows and writes them as the block's partial
 // (part[block][2][d]), no LDS pass.  The row sums meet in LDS (one barrier
-// per row, double-buffered), and the next row's dy and x are requested
-// before the current row's reduction (up to d = 4096), so a workgroup keeps
-// two rows of loads in flight.  (One wave per row with 64 columns per lane held 256 registers
+// per row, double-buffered), and the next row's dy, x and dres are requested
+// before the current row's reduction, so a workgroup keeps two rows of loads
+// in flight.  Bound by memory latency: 512 threads where the rows give a CU
+// few workgroups or 256 threads would hold more than 4096 columns (see the
+// dispatch; 2048 x 5120: 38.6 us with 256 threads and no rows ahead).
+// (One wave per row with 64 columns per lane held 256 registers
 // of column sums and row values: one wave per SIMD, 2.5 TB/s in the step.)
 constexpr int LNT_ROWS = 8;
 
-template <typename T, int NCH>
-__global__ void __launch_bounds__(256) ln_bwd_team_kernel(const T* __restrict__ dy, const float* __restrict__ x,
-                                                          const float* __restrict__ mean,
-                                                          const float* __restrict__ rstd, const T* __restrict__ gamma,
-                                                          float* __restrict__ dres, T* __restrict__ dres_lp,
-                                                          int accumulate, float* __restrict__ part, int64_t rows,
-                                                          int d) {
-  constexpr bool PF = NCH <= 4;
-  __shared__ float red[2][4][2];
+template <typename T, int NCH, int NT>
+__global__ void __launch_bounds__(NT) ln_bwd_team_kernel(const T* __restrict__ dy, const float* __restrict__ x,
+                                                         const float* __restrict__ mean,
+                                                         const float* __restrict__ rstd, const T* __restrict__ gamma,
+                                                         float* __restrict__ dres, T* __restrict__ dres_lp,
+                                                         int accumulate, float* __restrict__ part, int64_t rows,
+                                                         int d) {
+  constexpr int NW = NT / 64;
+  __shared__ float red[2][NW][2];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int64_t r0 = static_cast<int64_t>(blockIdx.x) * LNT_ROWS;
   const int nrow = static_cast<int>(min(static_cast<int64_t>(LNT_ROWS), rows - r0));
@@ -298,7 +301,7 @@ __global__ void __launch_bounds__(256) ln_bwd_team_kernel(const T* __restrict__ 
   float gam[NCH * 4], ca[NCH * 4], cb[NCH * 4];
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
-    const int c = 4 * tid + 1024 * j;
+    const int c = 4 * tid + 4 * NT * j;
     on[j] = c < d;
     Vec4<T> vg;
     if (on[j]) vg.load(gamma + c);
@@ -309,60 +312,42 @@ __global__ void __launch_bounds__(256) ln_bwd_team_kernel(const T* __restrict__ 
       cb[4 * j + i] = 0.f;
     }
   }
-  float gv[NCH * 4], xv[NCH * 4];
-  auto load_row = [&](int64_t row, float* g, float* xx) {
+  Vec4<T> gv[NCH], ng[NCH];
+  float4 xv[NCH], nx[NCH], pv[NCH], np[NCH];
+  float mu, r, nmu, nr;
+  auto load_row = [&](int64_t row, Vec4<T>* g, float4* xx, float4* pp, float& m_, float& r_) {
+    m_ = mean[row];
+    r_ = rstd[row];
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
       if (on[j]) {
-        const int c = 4 * tid + 1024 * j;
-        Vec4<T> vy;
-        vy.load(dy + row * d + c);
-        const float4 v = *reinterpret_cast<const float4*>(x + row * d + c);
-        const float xs[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          g[4 * j + i] = vy.get(i);
-          xx[4 * j + i] = xs[i];
-        }
+        const int c = 4 * tid + 4 * NT * j;
+        g[j].load(dy + row * d + c);
+        xx[j] = *reinterpret_cast<const float4*>(x + row * d + c);
+        if (accumulate) pp[j] = *reinterpret_cast<const float4*>(dres + row * d + c);
       }
     }
   };
-  load_row(r0, gv, xv);
+  load_row(r0, gv, xv, pv, mu, r);
   for (int k = 0; k < nrow; ++k) {
     const int64_t row = r0 + k;
-    const float mu = mean[row], r = rstd[row];
-    float* h = xv;  // xhat replaces x in place
+    if (k + 1 < nrow) load_row(row + 1, ng, nx, np, nmu, nr);
+    float h[NCH * 4];
     float sa = 0.f, sb = 0.f;
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
       if (on[j]) {
+        const float xs[4] = {xv[j].x, xv[j].y, xv[j].z, xv[j].w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int e = 4 * j + i;
-          h[e] = (xv[e] - mu) * r;
-          const float gp = gv[e] * gam[e];
+          const float g = gv[j].get(i);
+          h[e] = (xs[i] - mu) * r;
+          const float gp = g * gam[e];
           sa += gp;
           sb += gp * h[e];
-          ca[e] += gv[e] * h[e];
-          cb[e] += gv[e];
-        }
-      }
-    }
-    // the next row's loads go out now when the registers allow (PF)
-    float ng[PF ? NCH * 4 : 1], nx[PF ? NCH * 4 : 1];
-    if constexpr (PF) {
-      if (k + 1 < nrow) load_row(row + 1, ng, nx);
-    }
-    float prev[NCH * 4];
-    if (accumulate) {
-#pragma unroll
-      for (int j = 0; j < NCH; ++j) {
-        if (on[j]) {
-          const float4 v = *reinterpret_cast<const float4*>(dres + row * d + 4 * tid + 1024 * j);
-          prev[4 * j] = v.x;
-          prev[4 * j + 1] = v.y;
-          prev[4 * j + 2] = v.z;
-          prev[4 * j + 3] = v.w;
+          ca[e] += g * h[e];
+          cb[e] += g;
         }
       }
     }
@@ -374,38 +359,41 @@ __global__ void __launch_bounds__(256) ln_bwd_team_kernel(const T* __restrict__ 
       red[buf][w][1] = sb;
     }
     __syncthreads();
-    const float a = (((red[buf][0][0] + red[buf][1][0]) + red[buf][2][0]) + red[buf][3][0]) * inv_d;
-    const float b = (((red[buf][0][1] + red[buf][1][1]) + red[buf][2][1]) + red[buf][3][1]) * inv_d;
+    float a = red[buf][0][0], b = red[buf][0][1];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) {
+      a += red[buf][i][0];
+      b += red[buf][i][1];
+    }
+    a *= inv_d;
+    b *= inv_d;
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
       if (on[j]) {
-        const int c = 4 * tid + 1024 * j;
+        const int c = 4 * tid + 4 * NT * j;
+        const float ps[4] = {pv[j].x, pv[j].y, pv[j].z, pv[j].w};
         float o[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int e = 4 * j + i;
-          const float dx = r * (gv[e] * gam[e] - a - h[e] * b);
-          o[i] = accumulate ? prev[e] + dx : dx;
+          const float dx = r * (gv[j].get(i) * gam[e] - a - h[e] * b);
+          o[i] = accumulate ? ps[i] + dx : dx;
         }
         *reinterpret_cast<float4*>(dres + row * d + c) = make_float4(o[0], o[1], o[2], o[3]);
         if (dres_lp) Vec4<T>::store(dres_lp + row * d + c, o);
+        gv[j] = ng[j];
+        xv[j] = nx[j];
+        pv[j] = np[j];
       }
     }
-    if constexpr (PF) {
-#pragma unroll
-      for (int e = 0; e < NCH * 4; ++e) {
-        gv[e] = ng[e];
-        xv[e] = nx[e];
-      }
-    } else {
-      if (k + 1 < nrow) load_row(row + 1, gv, xv);
-    }
+    mu = nmu;
+    r = nr;
   }
   float* p = part + static_cast<int64_t>(blockIdx.x) * 2 * d;
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
     if (on[j]) {
-      const int c = 4 * tid + 1024 * j;
+      const int c = 4 * tid + 4 * NT * j;
       *reinterpret_cast<float4*>(p + c) = make_float4(ca[4 * j], ca[4 * j + 1], ca[4 * j + 2], ca[4 * j + 3]);
       *reinterpret_cast<float4*>(p + d + c) = make_float4(cb[4 * j], cb[4 * j + 1], cb[4 * j + 2], cb[4 * j + 3]);
     }
@@ -463,6 +451,51 @@ __global__ void __launch_bounds__(256) colsum_partial_kernel(const T* __restrict
   float s = 0.f;
   for (int64_t r = r0; r < r1; ++r) s += to_f<T>(x[r * ld + c]);
   part[static_cast<int64_t>(blockIdx.y) * cols + c] = s;
+}
+
+// Column sums of few rows in one launch: a workgroup owns 4 CQ columns; its
+// 256 / CQ row slices each add rows slice, slice + 256 / CQ, ... in order
+// (eight requested at a time), and the slice sums are added in slice order.
+template <typename T, typename TO, int CQ>
+__global__ void __launch_bounds__(256) colsum_few_rows_kernel(const T* __restrict__ x, int rows, int cols, int64_t ld,
+                                                              TO* __restrict__ out, int accumulate) {
+  constexpr int SL = 256 / CQ;
+  __shared__ float4 sh[SL][CQ];
+  const int q = threadIdx.x % CQ, sl = threadIdx.x / CQ, c = (blockIdx.x * CQ + q) * 4;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c < cols) {
+    auto add = [&](const Vec4<T>& v) {
+      s.x += v.get(0);
+      s.y += v.get(1);
+      s.z += v.get(2);
+      s.w += v.get(3);
+    };
+    int r = sl;
+    for (; r + 7 * SL < rows; r += 8 * SL) {
+      Vec4<T> v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i].load(x + static_cast<int64_t>(r + i * SL) * ld + c);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) add(v[i]);
+    }
+    for (; r < rows; r += SL) {
+      Vec4<T> v;
+      v.load(x + static_cast<int64_t>(r) * ld + c);
+      add(v);
+    }
+  }
+  sh[sl][q] = s;
+  __syncthreads();
+  // thread (column) j of the workgroup's 4 CQ: component j % 4 of quad j / 4
+  const int j = threadIdx.x, cj = blockIdx.x * 4 * CQ + j;
+  if (j < 4 * CQ && cj < cols) {
+    const float* f = reinterpret_cast<const float*>(&sh[0][0]) + j;
+    float t = f[0];
+#pragma unroll
+    for (int i = 1; i < SL; ++i) t += f[i * 4 * CQ];
+    if (accumulate) t += to_f<TO>(out[cj]);
+    out[cj] = from_f<TO>(t);
+  }
 }
 
 // out[c] (+)= sum over p of part[p * stride + c].  A workgroup owns 16
@@ -799,16 +832,20 @@ hipError_t ln_bwd_t(const void* dy, const float* x, const float* mean, const flo
   auto lp = static_cast<T*>(dres_lp);
   const int ac = acc ? 1 : 0;
   if (lnt_usable(d)) {
-    dim3 grid(static_cast<unsigned>((rows + LNT_ROWS - 1) / LNT_ROWS)), block(256);
-#define ATOM_LNT(CH)                                                                                             \
-  hipLaunchKernelGGL((ln_bwd_team_kernel<T, CH>), grid, block, 0, s, a0, x, mean, rstd, g, dres, lp, ac, part, rows, \
-                     d)
-    if (ne <= 4) ATOM_LNT(1);
-    else if (ne <= 8) ATOM_LNT(2);
-    else if (ne <= 12) ATOM_LNT(3);
-    else if (ne <= 16) ATOM_LNT(4);
-    else if (ne <= 20) ATOM_LNT(5);
-    else ATOM_LNT(8);
+    dim3 grid(static_cast<unsigned>((rows + LNT_ROWS - 1) / LNT_ROWS));
+#define ATOM_LNT(CH, NT_)                                                                                         \
+  hipLaunchKernelGGL((ln_bwd_team_kernel<T, CH, NT_>), grid, dim3(NT_), 0, s, a0, x, mean, rstd, g, dres, lp, ac, \
+                     part, rows, d)
+    // 512 threads beyond 4096 columns, and from 2048 on while 256 would leave
+    // a CU less than two workgroups
+    if (d > 4096 || (d > 2048 && grid.x < 512)) {
+      if (d <= 4096) ATOM_LNT(2, 512);
+      else if (d <= 6144) ATOM_LNT(3, 512);
+      else ATOM_LNT(4, 512);
+    } else if (ne <= 4) ATOM_LNT(1, 256);
+    else if (ne <= 8) ATOM_LNT(2, 256);
+    else if (ne <= 12) ATOM_LNT(3, 256);
+    else ATOM_LNT(4, 256);
 #undef ATOM_LNT
     return hipGetLastError();
   }
@@ -871,12 +908,15 @@ hipError_t layernorm_bwd(int dtype, const void* dy, const float* x, const float*
 
 int64_t colsum_blocks(int64_t rows) { return (rows + CS_ROWS - 1) / CS_ROWS; }
 
-hipError_t colsum_partial(int in_dtype, const void* x, int64_t rows, int cols, int64_t ld, float* part,
+// Rows of whole, aligned 4-vectors.
+static bool colsum_vec(int in_dtype, const void* x, int cols, int64_t ld) {
+  return cols % 4 == 0 && ld % 4 == 0 && reinterpret_cast<uintptr_t>(x) % (in_dtype == DT_BF16 ? 8 : 16) == 0;
+}
+
+static hipError_t colsum_partial(int in_dtype, const void* x, int64_t rows, int cols, int64_t ld, float* part,
                           hipStream_t s) {
   if (rows <= 0 || cols <= 0) return hipErrorInvalidValue;
-  const bool vec = cols % 4 == 0 && ld % 4 == 0 &&
-                   reinterpret_cast<uintptr_t>(x) % (in_dtype == DT_BF16 ? 8 : 16) == 0;
-  if (vec) {
+  if (colsum_vec(in_dtype, x, cols, ld)) {
     dim3 g4(static_cast<unsigned>((cols / 4 + 255) / 256), static_cast<unsigned>(colsum_blocks(rows))), b4(256);
     if (in_dtype == DT_BF16)
       hipLaunchKernelGGL(colsum_partial4_kernel<bf16_t>, g4, b4, 0, s, static_cast<const bf16_t*>(x), rows, cols,
@@ -912,6 +952,34 @@ hipError_t sum_parts2(const float* part, int64_t nparts, int cols, int64_t part_
 hipError_t sum_parts(const float* part, int64_t nparts, int cols, int64_t part_stride, int out_dtype, void* out,
                      bool accumulate, hipStream_t s) {
   return sum_parts2(part, nparts, cols, part_stride, out_dtype, out, out, cols, accumulate, s);
+}
+
+hipError_t colsum(int in_dtype, const void* x, int64_t rows, int cols, int64_t ld, float* part, int out_dtype,
+                  void* out, bool accumulate, hipStream_t s) {
+  if (rows <= 0 || cols <= 0) return hipErrorInvalidValue;
+  // One launch up to 1024 rows (520 x 2304: two launches of 4.7 and 3.9 us);
+  // beyond that the rows need more workgroups than the columns give.
+  if (rows <= 1024 && colsum_vec(in_dtype, x, cols, ld)) {
+    const int ac = accumulate ? 1 : 0, n = static_cast<int>(rows);
+#define ATOM_CF(T, TO, CQ)                                                                                        \
+  hipLaunchKernelGGL((colsum_few_rows_kernel<T, TO, CQ>), dim3(static_cast<unsigned>((cols + 4 * CQ - 1) / (4 * CQ))), \
+                     dim3(256), 0, s, static_cast<const T*>(x), n, cols, ld, static_cast<TO*>(out), ac)
+#define ATOM_CFQ(T, TO)                                                                                           \
+  do {                                                                                                            \
+    if (cols <= 4096) ATOM_CF(T, TO, 4);                                                                          \
+    else ATOM_CF(T, TO, 16);                                                                                      \
+  } while (0)
+    if (in_dtype == DT_BF16 && out_dtype == DT_BF16) ATOM_CFQ(bf16_t, bf16_t);
+    else if (in_dtype == DT_BF16) ATOM_CFQ(bf16_t, float);
+    else if (out_dtype == DT_BF16) ATOM_CFQ(float, bf16_t);
+    else ATOM_CFQ(float, float);
+#undef ATOM_CFQ
+#undef ATOM_CF
+    return hipGetLastError();
+  }
+  hipError_t e = colsum_partial(in_dtype, x, rows, cols, ld, part, s);
+  if (e != hipSuccess) return e;
+  return sum_parts(part, colsum_blocks(rows), cols, cols, out_dtype, out, accumulate, s);
 }
 
 hipError_t embed_fwd(int dtype, const int32_t* tok, const void* wte, const void* wpe, float* x, int64_t n_tok,
