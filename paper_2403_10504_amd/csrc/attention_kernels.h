@@ -364,9 +364,7 @@ __global__ void __launch_bounds__(256, ATOM_ATTN_FWD_OCC) attn_fwd_kernel(const 
 struct BlockId {
   int x, bh;
 };
-__device__ __forceinline__ BlockId attn_block(bool heavy_last) {
-  const int n_x = gridDim.x, n_bh = gridDim.y;
-  const int lin = blockIdx.y * n_x + blockIdx.x;
+__device__ __forceinline__ BlockId attn_block(int lin, int n_x, int n_bh, bool heavy_last) {
   int rank, bh;  // rank 0 = the heaviest block
   if ((n_bh & 7) == 0) {
     const int per = n_bh >> 3, i = lin >> 3;  // heads per XCD; item index inside the XCD
@@ -377,6 +375,9 @@ __device__ __forceinline__ BlockId attn_block(bool heavy_last) {
     bh = lin % n_bh;
   }
   return BlockId{heavy_last ? n_x - 1 - rank : rank, bh};
+}
+__device__ __forceinline__ BlockId attn_block(bool heavy_last) {
+  return attn_block(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, heavy_last);
 }
 
 // ------------------------------------------- forward, bf16, direct loads
@@ -415,8 +416,8 @@ struct FwdDL {
 // items less full); four with four waves of two groups at d_h 64, where 128
 // registers suffice and four workgroups fit the LDS (82 against 88 us at
 // GPT-3 Small's shape; five spill).
-template <int DH, int G, int NW>
-__global__ void __launch_bounds__(64 * NW, (DH == 64 || G == 1) ? 4 : 2)
+template <int DH, int G, int NW, int WPS>
+__global__ void __launch_bounds__(64 * NW, WPS)
     attn_fwd_dl_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int B, int Tn,
                        int H) {
   constexpr int NT = 64 * NW;
@@ -929,6 +930,21 @@ __global__ void __launch_bounds__(64 * NW, ATOM_ATTN_DQ_OCC) attn_bwd_dq_kernel(
   }
 }
 
+// One row's dot product of two operands held as row fragments: the lane's
+// elements, then the row's four lanes.
+template <int NS>
+__device__ __forceinline__ float row_dot(const Frag<bf16_t> (&x)[NS], const Frag<bf16_t> (&y)[NS]) {
+  float v = 0.f;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const uint32_t a[4] = {x[s].v.x, x[s].v.y, x[s].v.z, x[s].v.w}, c[4] = {y[s].v.x, y[s].v.y, y[s].v.z, y[s].v.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      v += bf2f(a[k] & 0xffff) * bf2f(c[k] & 0xffff) + bf2f(a[k] >> 16) * bf2f(c[k] >> 16);
+  }
+  return rows4_sum(v);
+}
+
 // ----------------------------------------- backward: dK, dV, bf16, direct loads
 // Q and dO tiles (natural layout) by direct loads, two stages; both are read
 // as row fragments (S = Q K^T, dP = dO V^T) and transposed in pair order
@@ -937,31 +953,30 @@ __global__ void __launch_bounds__(64 * NW, ATOM_ATTN_DQ_OCC) attn_bwd_dq_kernel(
 template <int DH>
 __device__ __forceinline__ int dsw(int r);
 
-// Launch bounds of both backward kernels: at d_h 64 four waves per SIMD (108
+// Launch bounds of the backward kernels: at d_h 64 four waves per SIMD (108
 // registers; two eight-wave workgroups per CU: 264 against 291 us for the
 // whole backward at GPT-3 Small's shape), at d_h 128 two (244 and 174
 // registers, one workgroup per CU; 128 registers would spill).
-template <int DH, int W>
-__global__ void __launch_bounds__(64 * W, DH == 64 ? 4 : 2) attn_bwd_dkdv_dl_kernel(const bf16_t* __restrict__ qkv,
-                                                                  const bf16_t* __restrict__ dout,
-                                                                  const float* __restrict__ lse,
-                                                                  const float* __restrict__ delta,
-                                                                  bf16_t* __restrict__ dqkv, int B, int Tn, int H) {
+//
+// OWN_D: D is computed here from O and dO, for every query the workgroup
+// visits, into d_own ([queries from the first tile on], LDS); otherwise it is
+// read from delta.
+template <int DH>
+constexpr int dkdv_stage() {
+  return 2 * FwdDL<DH>::TILE + 2 * BT * 4;  // Q, dO, LSE (log2 units), D of one 64-query tile
+}
+template <int DH, int W, int SUB, bool OWN_D>
+__device__ __forceinline__ void bwd_dkdv_dl(uint8_t* lds, float* d_own, const BlockId blk,
+                                            const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                            const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                            const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int Tn, int H) {
   using F = FwdDL<DH>;
   constexpr int NS = DH / 32, NCT = DH / 16, NT = 64 * W, RB = DH * 2, BKEYS = 16 * W;
   constexpr int LPT = F::TILE / (NT * 16);
   static_assert(LPT >= 1 && F::TILE % (NT * 16) == 0, "tile split");
-  constexpr int STAGE = 2 * F::TILE + 2 * BT * 4;  // Q, dO, LSE (log2 units), D of one 64-query tile
-  // Two query tiles per pipeline stage, so one barrier per 128 queries: the
-  // wave's work between barriers doubles (373 against 377 us for the whole
-  // backward at the 6.7B shape, 262 against 273 at d_h 64); the loop over
-  // the two stays rolled (unrolled, 40 bytes spill at d_h 128)
-  constexpr int SUB = 2;
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * SUB * STAGE];
-
+  constexpr int STAGE = dkdv_stage<DH>();
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const BlockId blk = attn_block(false);  // key block x sees the queries from x on
   const int bh = blk.bh, b = bh / H, h = bh % H;
   const int d = H * DH;
   const int64_t ld = 3 * static_cast<int64_t>(d);
@@ -1008,14 +1023,14 @@ __global__ void __launch_bounds__(64 * W, DH == 64 ? 4 : 2) attn_bwd_dkdv_dl_ker
     if (tid < SUB * BT) {
       const int i = i0 + tid;
       pre_lse = i < Tn ? lse_b[i] * LOG2E : INFINITY;
-      pre_del = i < Tn ? del_b[i] : 0.f;
+      if constexpr (!OWN_D) pre_del = i < Tn ? del_b[i] : 0.f;
     }
   };
   auto store_rows = [&](int st) {
     if (tid < SUB * BT) {
       float* rows = reinterpret_cast<float*>(lds + (st * SUB + tid / BT) * STAGE + 2 * F::TILE);
       rows[tid % BT] = pre_lse;
-      rows[BT + tid % BT] = pre_del;
+      if constexpr (!OWN_D) rows[BT + tid % BT] = pre_del;
     }
   };
   auto rowfrag = [&](Frag<bf16_t>& f, const uint8_t* st, int it, int s) {
@@ -1043,6 +1058,28 @@ __global__ void __launch_bounds__(64 * W, DH == 64 ? 4 : 2) attn_bwd_dkdv_dl_ker
     read_rows(qt0 * BT);
     store_rows(0);
   }
+  if constexpr (OWN_D) {
+    // 16 queries per wave and step, FLY steps' loads in flight; rows past the
+    // end are zeros.  The loop's first barrier makes d_own visible.
+    constexpr int FLY = 4;
+    const bf16_t* orow = o + static_cast<int64_t>(b) * Tn * d + h * DH;
+    for (int r0 = qt0 * BT; r0 < n_qt * BT; r0 += 16 * W * FLY) {
+      Frag<bf16_t> fo[FLY][NS], fd[FLY][NS];
+#pragma unroll
+      for (int f = 0; f < FLY; ++f)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          frag_global(fo[f][s], orow, d, r0 + 16 * (f * W + w) + lr, Tn, 32 * s + 8 * lg);
+          frag_global(fd[f][s], ob, d, r0 + 16 * (f * W + w) + lr, Tn, 32 * s + 8 * lg);
+        }
+#pragma unroll
+      for (int f = 0; f < FLY; ++f) {
+        const int r = r0 + 16 * (f * W + w) + lr;
+        const float v = row_dot<NS>(fo[f], fd[f]);
+        if (lg == 0 && r < n_qt * BT) d_own[r - qt0 * BT] = v;
+      }
+    }
+  }
   for (int qs0 = qt0; qs0 < n_qt; qs0 += SUB) {
     const int cur = ((qs0 - qt0) / SUB) & 1;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1061,7 +1098,7 @@ __global__ void __launch_bounds__(64 * W, DH == 64 ? 4 : 2) attn_bwd_dkdv_dl_ker
         const uint8_t* qs = lds + stg * STAGE;
         const uint8_t* os = qs + F::TILE;
         const float* lse_s = reinterpret_cast<const float*>(qs + 2 * F::TILE);
-        const float* del_s = lse_s + BT;
+        const float* del_s = OWN_D ? d_own + (qt - qt0) * BT : lse_s + BT;
         float p[4][4], ds[4][4];
         const bool mask = i0 < kw + 15 || tail_keys;  // diagonal tile or keys past the end
         if constexpr (DH == 128) {
@@ -1187,26 +1224,18 @@ __device__ __forceinline__ int dsw(int r) {
   return DH == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3);
 }
 
-template <int DH, int NW>
-__global__ void __launch_bounds__(64 * NW, DH == 64 ? 4 : 2) attn_bwd_dq_dl_kernel(const bf16_t* __restrict__ qkv,
-                                                                const bf16_t* __restrict__ o,
-                                                                const bf16_t* __restrict__ dout,
-                                                                const float* __restrict__ lse,
-                                                                float* __restrict__ delta,
-                                                                bf16_t* __restrict__ dqkv, int B, int Tn, int H) {
+template <int DH, int NW, int SUB>
+__device__ __forceinline__ void bwd_dq_dl(uint8_t* lds, const BlockId blk, const bf16_t* __restrict__ qkv,
+                                          const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
+                                          const float* __restrict__ lse, float* __restrict__ delta,
+                                          bf16_t* __restrict__ dqkv, int Tn, int H) {
   using F = FwdDL<DH>;
   constexpr int NS = DH / 32, NCT = DH / 16, BQ = NW * 16, NT = 64 * NW, RB = DH * 2;
   constexpr int LPT = F::TILE / (NT * 16);  // direct loads per thread per tile and operand
   static_assert(LPT >= 1 && F::TILE % (NT * 16) == 0, "tile split");
-  // Two key tiles per pipeline stage, one barrier per 128 keys (at d_h 64
-  // 254-260 against 272 us for the whole backward at GPT-3 Small's shape;
-  // unchanged at d_h 128, where one workgroup per CU leaves the LDS for it)
-  constexpr int SUB = 2;
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * SUB * F::STAGE];
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const BlockId blk = attn_block(true);
   const int bh = blk.bh, b = bh / H, h = bh % H;
   const int d = H * DH;
   const int64_t ld = 3 * static_cast<int64_t>(d);
@@ -1265,19 +1294,13 @@ __global__ void __launch_bounds__(64 * NW, DH == 64 ? 4 : 2) attn_bwd_dq_dl_kern
   // four lane rows; kept for the dK/dV kernel, which runs after this one.
   // (As a kernel of its own D read dO once more and cost a launch: 12.7 of
   // 340 us of the backward at the 6.7B shape, 4 of 33 at three sequences of 333.)
-  float del_i = 0.f;
+  float del_i;
   {
     const bf16_t* orow = o + static_cast<int64_t>(b) * Tn * d + h * DH;
+    Frag<bf16_t> f[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      Frag<bf16_t> f;
-      frag_global(f, orow, d, qi, Tn, 32 * s + 8 * lg);
-      const uint32_t a[4] = {f.v.x, f.v.y, f.v.z, f.v.w}, c[4] = {of[s].v.x, of[s].v.y, of[s].v.z, of[s].v.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        del_i += bf2f(a[k] & 0xffff) * bf2f(c[k] & 0xffff) + bf2f(a[k] >> 16) * bf2f(c[k] >> 16);
-    }
-    del_i = rows4_sum(del_i);
+    for (int s = 0; s < NS; ++s) frag_global(f[s], orow, d, qi, Tn, 32 * s + 8 * lg);
+    del_i = row_dot<NS>(f, of);
     if (lg == 0 && qi < Tn) delta[(static_cast<int64_t>(b) * H + h) * Tn + qi] = del_i;
   }
   for (int ks0 = 0; ks0 < n_kt; ks0 += SUB) {
@@ -1357,6 +1380,57 @@ __global__ void __launch_bounds__(64 * NW, DH == 64 ? 4 : 2) attn_bwd_dq_dl_kern
   }
 }
 
+// Two tiles per pipeline stage, so one barrier per 128 rows: a wave's work
+// between barriers doubles (dK/dV: 373 against 377 us for the whole backward
+// at the 6.7B shape, 262 against 273 at d_h 64; dQ: 254-260 against 272 us at
+// GPT-3 Small's shape, unchanged at d_h 128, where one workgroup per CU leaves
+// the LDS for it); the loop over the two stays rolled (unrolled, 40 bytes
+// spill at d_h 128).
+template <int DH, int W>
+__global__ void __launch_bounds__(64 * W, DH == 64 ? 4 : 2)
+    attn_bwd_dkdv_dl_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+                            const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv,
+                            int B, int Tn, int H) {
+  constexpr int SUB = 2;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * SUB * dkdv_stage<DH>()];
+  // key block x sees the queries from x on
+  bwd_dkdv_dl<DH, W, SUB, false>(lds, nullptr, attn_block(false), qkv, nullptr, dout, lse, delta, dqkv, Tn, H);
+}
+
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW, DH == 64 ? 4 : 2)
+    attn_bwd_dq_dl_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
+                          const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int B,
+                          int Tn, int H) {
+  constexpr int SUB = 2;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * SUB * FwdDL<DH>::STAGE];
+  bwd_dq_dl<DH, NW, SUB>(lds, attn_block(true), qkv, o, dout, lse, delta, dqkv, Tn, H);
+}
+
+// Backward of a small problem in one launch.  With few heads or short ones,
+// 128-row workgroups leave CUs idle and a kernel lasts as long as its longest
+// chain of tiles (T 2048, 4 heads: 64 workgroups, dQ 50 us, then dK/dV 60), so
+// here the workgroups have four waves (64 keys or queries, one tile per stage:
+// two share a CU at d_h 128, three at d_h 64), the first half of the grid does
+// dK/dV and the second dQ side by side, and dK/dV computes D itself (one read
+// of O and dO from its first tile on, 256 rows' loads in flight), with the dQ
+// kernel's arithmetic, so the results are the same bits.
+constexpr int SMALL_BWD_MAX_T = 2048;  // queries whose D fits beside the stages
+template <int DH>
+__global__ void __launch_bounds__(256, DH == 64 ? 3 : 2)
+    attn_bwd_small_dl_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                             const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                             float* __restrict__ delta, bf16_t* __restrict__ dqkv, int n_x, int n_bh, int Tn, int H) {
+  static_assert(2 * dkdv_stage<DH>() >= 2 * FwdDL<DH>::STAGE, "stages");
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * dkdv_stage<DH>() + SMALL_BWD_MAX_T * 4];
+  const int total = n_x * n_bh, id = blockIdx.x;
+  if (id < total)
+    bwd_dkdv_dl<DH, 4, 1, true>(lds, reinterpret_cast<float*>(lds + 2 * dkdv_stage<DH>()),
+                                attn_block(id, n_x, n_bh, false), qkv, o, dout, lse, nullptr, dqkv, Tn, H);
+  else
+    bwd_dq_dl<DH, 4, 1>(lds, attn_block(id - total, n_x, n_bh, true), qkv, o, dout, lse, delta, dqkv, Tn, H);
+}
+
 // Query groups per wave in the forward (G), waves per dK/dV workgroup (W),
 // and query groups (GQ) and waves (WQ) of the dQ kernel; bf16 takes the
 // direct-load kernels, fp32 the register-staged ones.  dQ: eight waves of 16
@@ -1378,14 +1452,45 @@ struct ACfg {
   static constexpr int WQ = sizeof(T) == 2 ? 8 : 4;
 };
 
+// Where the small variants (64-row workgroups) are taken; n64 = 64-row blocks
+// of all heads, times in us of forward + backward, large variants -> small.
+// Forward (four waves of 16 queries): d_h 128 up to one workgroup per CU (T 1000, 16 heads, n64 256: 85.7 ->
+// 82.6; n64 288 at T 1500 118.9 -> 122.1, 1280 254.6 -> 268.2); d_h 64, where
+// five share a CU, up to five per CU (n64 1280: 150.7 -> 146.0, 768: 125.5 ->
+// 118.3; 1536 even, 3072 298.1 -> 303.3).
+template <int DH>
+bool small_fwd(int B, int Tn, int H) {
+  return static_cast<int64_t>(B) * H * ((Tn + 63) / 64) <= (DH == 128 ? 256 : 1280);
+}
+// Backward: while dK/dV and dQ side by side take at most two rounds of the
+// resident workgroups (two per CU at d_h 128, three at d_h 64): d_h 128, T
+// 2048, n64 128 / 512 / 768: 150.5 -> 120.1, 158.0 -> 144.6, 166.8 -> 196.8;
+// T 333, n64 288: 42.2 -> 34.0; d_h 64, T 2048, n64 128 / 768 / 1280: 108.4 ->
+// 84.7, 125.5 -> 118.5, 150.7 -> 169.0.  Heads of 65 to 128 rows fill one
+// 128-row workgroup but two of 64, so at d_h 128, where those run in one
+// round, they are worth one round only (T 128, n64 32: 24.8 -> 17.1, 448: 30.4
+// -> 31.5; T 65, n64 500: 23.9 -> 30.2).
+template <int DH>
+bool small_bwd(int B, int Tn, int H) {
+  const int64_t n64 = static_cast<int64_t>(B) * H * ((Tn + 63) / 64);
+  if (Tn > SMALL_BWD_MAX_T) return false;
+  if (DH == 64) return n64 <= 768;
+  return n64 <= (Tn > 64 && Tn <= 128 ? 256 : 512);
+}
+
 template <typename T, int DH>
 hipError_t fwd_t(const void* qkv, void* o, float* lse, int B, int Tn, int H, hipStream_t s) {
   constexpr int G = ACfg<T, DH>::G;
   if constexpr (sizeof(T) == 2) {
     constexpr int FG = DH == 128 ? ATOM_FWD_G128 : 2, FNW = DH == 128 ? ATOM_FWD_NW128 : 4;
+    if (small_fwd<DH>(B, Tn, H)) {
+      hipLaunchKernelGGL((attn_fwd_dl_kernel<DH, 1, 4, 2>), dim3((Tn + 63) / 64, B * H), dim3(256), 0, s,
+                         static_cast<const bf16_t*>(qkv), static_cast<bf16_t*>(o), lse, B, Tn, H);
+      return hipGetLastError();
+    }
     dim3 grid((Tn + 16 * FG * FNW - 1) / (16 * FG * FNW), B * H), block(64 * FNW);
-    hipLaunchKernelGGL((attn_fwd_dl_kernel<DH, FG, FNW>), grid, block, 0, s, static_cast<const bf16_t*>(qkv),
-                       static_cast<bf16_t*>(o), lse, B, Tn, H);
+    hipLaunchKernelGGL((attn_fwd_dl_kernel<DH, FG, FNW, (DH == 64 || FG == 1) ? 4 : 2>), grid, block, 0, s,
+                       static_cast<const bf16_t*>(qkv), static_cast<bf16_t*>(o), lse, B, Tn, H);
   } else {
     dim3 grid((Tn + 64 * G - 1) / (64 * G), B * H), block(256);
     hipLaunchKernelGGL((attn_fwd_kernel<T, DH, G>), grid, block, 0, s, static_cast<const T*>(qkv), static_cast<T*>(o),
@@ -1399,6 +1504,13 @@ hipError_t bwd_t(const void* qkv, const void* o, const void* dout, const float* 
                  int Tn, int H, hipStream_t s) {
   constexpr int W = ACfg<T, DH>::W, GQ = ACfg<T, DH>::GQ, WQ = ACfg<T, DH>::WQ;
   if constexpr (sizeof(T) == 2) {
+    if (small_bwd<DH>(B, Tn, H)) {
+      const int n_x = (Tn + 63) / 64;
+      hipLaunchKernelGGL(attn_bwd_small_dl_kernel<DH>, dim3(2u * n_x * B * H), dim3(256), 0, s,
+                         static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o),
+                         static_cast<const bf16_t*>(dout), lse, delta, static_cast<bf16_t*>(dqkv), n_x, B * H, Tn, H);
+      return hipGetLastError();
+    }
     // dQ first: it computes D
     hipLaunchKernelGGL((attn_bwd_dq_dl_kernel<DH, WQ>), dim3((Tn + 16 * WQ - 1) / (16 * WQ), B * H), dim3(64 * WQ), 0,
                        s, static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o),
