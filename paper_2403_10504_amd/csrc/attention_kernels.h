@@ -407,7 +407,8 @@ struct FwdDL {
   __device__ static int vswz(int r) { return DH == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); }
 };
 
-// NW waves of G groups of 16 queries per workgroup.  Waves per SIMD the
+// NW waves of G groups of 16 queries per workgroup (KS = 2: two such sets of
+// waves, taking alternate key tiles; their sums meet at the end).  Waves per SIMD the
 // register allocation must allow (the second launch bound): four with eight
 // waves of one group (d_h 128: two workgroups per CU, as the LDS allows, in
 // 128 registers with a spill of nine; against four waves of two groups at two
@@ -416,14 +417,14 @@ struct FwdDL {
 // items less full); four with four waves of two groups at d_h 64, where 128
 // registers suffice and four workgroups fit the LDS (82 against 88 us at
 // GPT-3 Small's shape; five spill).
-template <int DH, int G, int NW, int WPS>
-__global__ void __launch_bounds__(64 * NW, WPS)
+template <int DH, int G, int NW, int WPS, int KS = 1>
+__global__ void __launch_bounds__(64 * NW * KS, WPS)
     attn_fwd_dl_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int B, int Tn,
                        int H) {
-  constexpr int NT = 64 * NW;
+  constexpr int NT = 64 * NW * KS;
   using F = FwdDL<DH, NT>;
   constexpr int NS = DH / 32, NCT = DH / 16, BQ = NW * 16 * G, RB = DH * 2;
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * F::STAGE];
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * KS * F::STAGE];
 
   // the wave index through readfirstlane, so that everything derived from
   // it (the wave's queries, the diagonal test) is known to be wave-uniform
@@ -437,7 +438,8 @@ __global__ void __launch_bounds__(64 * NW, WPS)
   const bf16_t* kb = qb + d;
   const bf16_t* vb = qb + 2 * d;
   const int q0 = blk.x * BQ;
-  const int qw = q0 + w * 16 * G;
+  const int part = w / NW;  // split of the key tiles
+  const int qw = q0 + (w - part * NW) * 16 * G;
   const float sc = LOG2E / sqrtf(static_cast<float>(DH));
 
   Frag<bf16_t> qf[G][NS];
@@ -502,17 +504,23 @@ __global__ void __launch_bounds__(64 * NW, WPS)
   };
 
   const int n_kt = min((Tn + BT - 1) / BT, (min(q0 + BQ, Tn) - 1) / BT + 1);
-  load_tile(0, 0);
-  for (int kt = 0; kt < n_kt; ++kt) {
-    const int j0 = kt * BT, cur = kt & 1;
-    // tile kt has landed for every wave, and every wave is done with tile kt-1
+  // KS tiles per stage, one for each split
+  auto load_stage = [&](int st, int kt) {
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+      if (kt + u < n_kt) load_tile(st * KS + u, (kt + u) * BT);
+  };
+  load_stage(0, 0);
+  for (int k0 = 0; k0 < n_kt; k0 += KS) {
+    const int kt = k0 + part, j0 = kt * BT, cur = (k0 / KS) & 1;
+    // tile kt has landed for every wave, and every wave is done with the stage before
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     asm volatile("s_barrier" ::: "memory");
-    if (kt + 1 < n_kt) load_tile(cur ^ 1, j0 + BT);
-    const uint8_t* ks = lds + cur * F::STAGE;
+    if (k0 + KS < n_kt) load_stage(cur ^ 1, k0 + KS);
+    const uint8_t* ks = lds + (cur * KS + part) * F::STAGE;
     const uint8_t* vs = ks + F::TILE;
-    if (j0 <= qw + 16 * G - 1) {
+    if (kt < n_kt && j0 <= qw + 16 * G - 1) {
       float p[G][4][4];
       float mloc[G];
 #pragma unroll
@@ -596,6 +604,28 @@ __global__ void __launch_bounds__(64 * NW, WPS)
     }
   }
 
+  if constexpr (KS > 1) {
+    // the second group's sums come to the first's reference maximum through
+    // LDS (a group that saw no key has m = -1e30 and zeros)
+    static_assert(KS == 2 && G == 1, "two groups");
+    f32x4_t* buf = reinterpret_cast<f32x4_t*>(lds);
+    float* ml = reinterpret_cast<float*>(buf + NCT * 64 * NW);
+    const int t = (w - part * NW) * 64 + lane;
+    __syncthreads();
+    if (part) {
+#pragma unroll
+      for (int c = 0; c < NCT; ++c) buf[c * (64 * NW) + t] = acc_o[0][c];
+      ml[t] = m_i[0];
+      ml[64 * NW + t] = l_i[0];
+    }
+    __syncthreads();
+    if (part) return;
+    const float m1 = ml[t], m_new = fmaxf(m_i[0], m1), a0 = ex2(m_i[0] - m_new), a1 = ex2(m1 - m_new);
+    m_i[0] = m_new;
+    l_i[0] = l_i[0] * a0 + ml[64 * NW + t] * a1;
+#pragma unroll
+    for (int c = 0; c < NCT; ++c) acc_o[0][c] = acc_o[0][c] * a0 + buf[c * (64 * NW) + t] * a1;
+  }
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     const int qi = qw + g * 16 + lr;
@@ -930,6 +960,34 @@ __global__ void __launch_bounds__(64 * NW, ATOM_ATTN_DQ_OCC) attn_bwd_dq_kernel(
   }
 }
 
+// Where KS = 2 groups of W waves share a workgroup's rows and took alternate
+// tiles: adds the second group's accumulators to the first's through LDS (the
+// stages, which every wave is done with after the first barrier).  x and y may
+// be the same array, then it is added once.
+template <int W, int KS, int N>
+__device__ __forceinline__ void sum_splits(uint8_t* lds, f32x4_t (&x)[N], f32x4_t (&y)[N], int w, int lane) {
+  static_assert(KS == 2, "two groups");
+  f32x4_t* buf = reinterpret_cast<f32x4_t*>(lds);
+  const int t = (w >= W ? w - W : w) * 64 + lane;
+  const bool two = &x != &y;
+  __syncthreads();
+  if (w >= W) {
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      buf[c * (64 * W) + t] = x[c];
+      if (two) buf[(N + c) * (64 * W) + t] = y[c];
+    }
+  }
+  __syncthreads();
+  if (w < W) {
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      x[c] += buf[c * (64 * W) + t];
+      if (two) y[c] += buf[(N + c) * (64 * W) + t];
+    }
+  }
+}
+
 // One row's dot product of two operands held as row fragments: the lane's
 // elements, then the row's four lanes.
 template <int NS>
@@ -965,14 +1023,15 @@ template <int DH>
 constexpr int dkdv_stage() {
   return 2 * FwdDL<DH>::TILE + 2 * BT * 4;  // Q, dO, LSE (log2 units), D of one 64-query tile
 }
-template <int DH, int W, int SUB, bool OWN_D>
+template <int DH, int W, int SUB, bool OWN_D, int KS = 1>
 __device__ __forceinline__ void bwd_dkdv_dl(uint8_t* lds, float* d_own, const BlockId blk,
                                             const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                             const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                             const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int Tn, int H) {
   using F = FwdDL<DH>;
-  constexpr int NS = DH / 32, NCT = DH / 16, NT = 64 * W, RB = DH * 2, BKEYS = 16 * W;
+  constexpr int NS = DH / 32, NCT = DH / 16, NT = 64 * W * KS, RB = DH * 2, BKEYS = 16 * W;
   constexpr int LPT = F::TILE / (NT * 16);
+  static_assert(KS == 1 || KS == SUB, "a tile of each stage per split");
   static_assert(LPT >= 1 && F::TILE % (NT * 16) == 0, "tile split");
   constexpr int STAGE = dkdv_stage<DH>();
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -987,8 +1046,9 @@ __device__ __forceinline__ void bwd_dkdv_dl(uint8_t* lds, float* d_own, const Bl
   const float* lse_b = lse + (static_cast<int64_t>(b) * H + h) * Tn;
   const float* del_b = delta + (static_cast<int64_t>(b) * H + h) * Tn;
   const int k0 = blk.x * BKEYS;
-  const int kw = k0 + w * 16;  // this wave's first key
-  const int kj = kw + lr;      // this lane's key
+  const int part = w / W;                // split of the query tiles
+  const int kw = k0 + (w - part * W) * 16;  // this wave's first key
+  const int kj = kw + lr;                // this lane's key
   const float sc = LOG2E / sqrtf(static_cast<float>(DH));
 
   Frag<bf16_t> kf[NS], vf[NS];
@@ -1063,18 +1123,18 @@ __device__ __forceinline__ void bwd_dkdv_dl(uint8_t* lds, float* d_own, const Bl
     // end are zeros.  The loop's first barrier makes d_own visible.
     constexpr int FLY = 4;
     const bf16_t* orow = o + static_cast<int64_t>(b) * Tn * d + h * DH;
-    for (int r0 = qt0 * BT; r0 < n_qt * BT; r0 += 16 * W * FLY) {
+    for (int r0 = qt0 * BT; r0 < n_qt * BT; r0 += 16 * W * KS * FLY) {
       Frag<bf16_t> fo[FLY][NS], fd[FLY][NS];
 #pragma unroll
       for (int f = 0; f < FLY; ++f)
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-          frag_global(fo[f][s], orow, d, r0 + 16 * (f * W + w) + lr, Tn, 32 * s + 8 * lg);
-          frag_global(fd[f][s], ob, d, r0 + 16 * (f * W + w) + lr, Tn, 32 * s + 8 * lg);
+          frag_global(fo[f][s], orow, d, r0 + 16 * (f * W * KS + w) + lr, Tn, 32 * s + 8 * lg);
+          frag_global(fd[f][s], ob, d, r0 + 16 * (f * W * KS + w) + lr, Tn, 32 * s + 8 * lg);
         }
 #pragma unroll
       for (int f = 0; f < FLY; ++f) {
-        const int r = r0 + 16 * (f * W + w) + lr;
+        const int r = r0 + 16 * (f * W * KS + w) + lr;
         const float v = row_dot<NS>(fo[f], fd[f]);
         if (lg == 0 && r < n_qt * BT) d_own[r - qt0 * BT] = v;
       }
@@ -1091,7 +1151,7 @@ __device__ __forceinline__ void bwd_dkdv_dl(uint8_t* lds, float* d_own, const Bl
       read_rows((qs0 + SUB) * BT);
     }
 #pragma unroll 1
-    for (int u = 0; u < SUB; ++u) {
+    for (int u = KS > 1 ? part : 0; u < (KS > 1 ? part + 1 : SUB); ++u) {
       const int qt = qs0 + u, i0 = qt * BT, stg = cur * SUB + u;
       if (qt >= n_qt) break;
       if (i0 + BT - 1 >= kw && kw < Tn) {  // some query of the tile sees some key of this wave
@@ -1193,6 +1253,10 @@ __device__ __forceinline__ void bwd_dkdv_dl(uint8_t* lds, float* d_own, const Bl
     }
     if (more) store_rows(cur ^ 1);
   }
+  if constexpr (KS > 1) {
+    sum_splits<W, KS>(lds, acc_dk, acc_dv, w, lane);
+    if (part != 0) return;
+  }
 
   if (kj < Tn) {
     const float scale = 1.f / sqrtf(static_cast<float>(DH));
@@ -1224,14 +1288,15 @@ __device__ __forceinline__ int dsw(int r) {
   return DH == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3);
 }
 
-template <int DH, int NW, int SUB>
+template <int DH, int NW, int SUB, int KS = 1>
 __device__ __forceinline__ void bwd_dq_dl(uint8_t* lds, const BlockId blk, const bf16_t* __restrict__ qkv,
                                           const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
                                           const float* __restrict__ lse, float* __restrict__ delta,
                                           bf16_t* __restrict__ dqkv, int Tn, int H) {
   using F = FwdDL<DH>;
-  constexpr int NS = DH / 32, NCT = DH / 16, BQ = NW * 16, NT = 64 * NW, RB = DH * 2;
+  constexpr int NS = DH / 32, NCT = DH / 16, BQ = NW * 16, NT = 64 * NW * KS, RB = DH * 2;
   constexpr int LPT = F::TILE / (NT * 16);  // direct loads per thread per tile and operand
+  static_assert(KS == 1 || KS == SUB, "a tile of each stage per split");
   static_assert(LPT >= 1 && F::TILE % (NT * 16) == 0, "tile split");
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1244,7 +1309,8 @@ __device__ __forceinline__ void bwd_dq_dl(uint8_t* lds, const BlockId blk, const
   const bf16_t* vb = qb + 2 * d;
   const bf16_t* ob = dout + static_cast<int64_t>(b) * Tn * d + h * DH;
   const int q0 = blk.x * BQ;
-  const int qw = q0 + w * 16;
+  const int part = w / NW;  // split of the key tiles
+  const int qw = q0 + (w - part * NW) * 16;
   const int qi = qw + lr;
   const float sc = LOG2E / sqrtf(static_cast<float>(DH));
 
@@ -1301,7 +1367,7 @@ __device__ __forceinline__ void bwd_dq_dl(uint8_t* lds, const BlockId blk, const
 #pragma unroll
     for (int s = 0; s < NS; ++s) frag_global(f[s], orow, d, qi, Tn, 32 * s + 8 * lg);
     del_i = row_dot<NS>(f, of);
-    if (lg == 0 && qi < Tn) delta[(static_cast<int64_t>(b) * H + h) * Tn + qi] = del_i;
+    if (lg == 0 && qi < Tn && part == 0) delta[(static_cast<int64_t>(b) * H + h) * Tn + qi] = del_i;
   }
   for (int ks0 = 0; ks0 < n_kt; ks0 += SUB) {
     const int cur = (ks0 / SUB) & 1;
@@ -1310,7 +1376,7 @@ __device__ __forceinline__ void bwd_dq_dl(uint8_t* lds, const BlockId blk, const
     asm volatile("s_barrier" ::: "memory");
     if (ks0 + SUB < n_kt) load_stage(cur ^ 1, ks0 + SUB);
 #pragma unroll 1
-    for (int u = 0; u < SUB; ++u) {
+    for (int u = KS > 1 ? part : 0; u < (KS > 1 ? part + 1 : SUB); ++u) {
       const int kt = ks0 + u, j0 = kt * BT, stg = cur * SUB + u;
       if (kt >= n_kt) break;
       if (j0 <= qw + 15) {
@@ -1369,6 +1435,10 @@ __device__ __forceinline__ void bwd_dq_dl(uint8_t* lds, const BlockId blk, const
     }
   }
 
+  if constexpr (KS > 1) {
+    sum_splits<NW, KS>(lds, acc_dq, acc_dq, w, lane);
+    if (part != 0) return;
+  }
   if (qi < Tn) {
     const float scale = 1.f / sqrtf(static_cast<float>(DH));
     bf16_t* row = dqkv + (static_cast<int64_t>(b) * Tn + qi) * ld + h * DH;
@@ -1414,21 +1484,23 @@ __global__ void __launch_bounds__(64 * NW, DH == 64 ? 4 : 2)
 // two share a CU at d_h 128, three at d_h 64), the first half of the grid does
 // dK/dV and the second dQ side by side, and dK/dV computes D itself (one read
 // of O and dO from its first tile on, 256 rows' loads in flight), with the dQ
-// kernel's arithmetic, so the results are the same bits.
+// kernel's arithmetic, so the results are the same bits.  KS = 2: eight waves,
+// two groups of four that share the rows and take alternate tiles.
 constexpr int SMALL_BWD_MAX_T = 2048;  // queries whose D fits beside the stages
-template <int DH>
-__global__ void __launch_bounds__(256, DH == 64 ? 3 : 2)
+template <int DH, int KS>
+__global__ void __launch_bounds__(256 * KS, KS == 1 && DH == 64 ? 3 : 2)
     attn_bwd_small_dl_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                              const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                              float* __restrict__ delta, bf16_t* __restrict__ dqkv, int n_x, int n_bh, int Tn, int H) {
-  static_assert(2 * dkdv_stage<DH>() >= 2 * FwdDL<DH>::STAGE, "stages");
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * dkdv_stage<DH>() + SMALL_BWD_MAX_T * 4];
+  constexpr int STAGES = 2 * KS * dkdv_stage<DH>();
+  static_assert(dkdv_stage<DH>() >= FwdDL<DH>::STAGE, "stages");
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGES + SMALL_BWD_MAX_T * 4];
   const int total = n_x * n_bh, id = blockIdx.x;
   if (id < total)
-    bwd_dkdv_dl<DH, 4, 1, true>(lds, reinterpret_cast<float*>(lds + 2 * dkdv_stage<DH>()),
-                                attn_block(id, n_x, n_bh, false), qkv, o, dout, lse, nullptr, dqkv, Tn, H);
+    bwd_dkdv_dl<DH, 4, KS, true, KS>(lds, reinterpret_cast<float*>(lds + STAGES), attn_block(id, n_x, n_bh, false),
+                                     qkv, o, dout, lse, nullptr, dqkv, Tn, H);
   else
-    bwd_dq_dl<DH, 4, 1>(lds, attn_block(id - total, n_x, n_bh, true), qkv, o, dout, lse, delta, dqkv, Tn, H);
+    bwd_dq_dl<DH, 4, KS, KS>(lds, attn_block(id - total, n_x, n_bh, true), qkv, o, dout, lse, delta, dqkv, Tn, H);
 }
 
 // Query groups per wave in the forward (G), waves per dK/dV workgroup (W),
@@ -1478,14 +1550,39 @@ bool small_bwd(int B, int Tn, int H) {
   return n64 <= (Tn > 64 && Tn <= 128 ? 256 : 512);
 }
 
+// Where a small problem's workgroups are doubled, two groups of four waves
+// taking alternate tiles (forward and backward as above, unsplit -> split).
+// It halves a chain of tiles where CUs have waves to spare, and costs a second
+// copy of the row fragments and the sum at the end.  Forward: while every
+// workgroup is resident (one per CU at d_h 128, two at d_h 64) and beyond 256
+// rows (d_h 128, T 2048, n64 256: 124.5 -> 115.8, n64 128 at T 512 37.4 ->
+// 36.0; T 200 within 0.3, T 64 12.3 -> 13.2; d_h 64, T 2048, n64 512: 93.6 ->
+// 88.7).
+template <int DH>
+bool split_fwd(int B, int Tn, int H) {
+  return Tn > 256 && static_cast<int64_t>(B) * H * ((Tn + 63) / 64) <= (DH == 128 ? 256 : 512);
+}
+// Backward: one round of half its grid, or two of long chains (T 2048, n64 128
+// / 192 / 256 at d_h 128: 116.5 -> 103.7, 132.4 -> 112.9, 124.5 -> 104.8; T
+// 1000, n64 256 / 320: 67.9 -> 60.3, 81.5 -> 82.3; T 512, n64 128 / 256: 37.4 ->
+// 35.0, 40.4 -> 41.5; T 333, n64 192 / 288: 32.0 -> 28.2, 35.5 -> 39.1; T 200,
+// n64 192: 24.3 -> 25.6; d_h 64 alike).
+inline bool split_bwd(int B, int Tn, int H) {
+  return Tn > 256 && static_cast<int64_t>(B) * H * ((Tn + 63) / 64) <= (Tn >= 1000 ? 256 : 192);
+}
+
 template <typename T, int DH>
 hipError_t fwd_t(const void* qkv, void* o, float* lse, int B, int Tn, int H, hipStream_t s) {
   constexpr int G = ACfg<T, DH>::G;
   if constexpr (sizeof(T) == 2) {
     constexpr int FG = DH == 128 ? ATOM_FWD_G128 : 2, FNW = DH == 128 ? ATOM_FWD_NW128 : 4;
     if (small_fwd<DH>(B, Tn, H)) {
-      hipLaunchKernelGGL((attn_fwd_dl_kernel<DH, 1, 4, 2>), dim3((Tn + 63) / 64, B * H), dim3(256), 0, s,
-                         static_cast<const bf16_t*>(qkv), static_cast<bf16_t*>(o), lse, B, Tn, H);
+      if (split_fwd<DH>(B, Tn, H))
+        hipLaunchKernelGGL((attn_fwd_dl_kernel<DH, 1, 4, 2, 2>), dim3((Tn + 63) / 64, B * H), dim3(512), 0, s,
+                           static_cast<const bf16_t*>(qkv), static_cast<bf16_t*>(o), lse, B, Tn, H);
+      else
+        hipLaunchKernelGGL((attn_fwd_dl_kernel<DH, 1, 4, 2>), dim3((Tn + 63) / 64, B * H), dim3(256), 0, s,
+                           static_cast<const bf16_t*>(qkv), static_cast<bf16_t*>(o), lse, B, Tn, H);
       return hipGetLastError();
     }
     dim3 grid((Tn + 16 * FG * FNW - 1) / (16 * FG * FNW), B * H), block(64 * FNW);
@@ -1506,9 +1603,14 @@ hipError_t bwd_t(const void* qkv, const void* o, const void* dout, const float* 
   if constexpr (sizeof(T) == 2) {
     if (small_bwd<DH>(B, Tn, H)) {
       const int n_x = (Tn + 63) / 64;
-      hipLaunchKernelGGL(attn_bwd_small_dl_kernel<DH>, dim3(2u * n_x * B * H), dim3(256), 0, s,
-                         static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o),
-                         static_cast<const bf16_t*>(dout), lse, delta, static_cast<bf16_t*>(dqkv), n_x, B * H, Tn, H);
+      auto launch = [&](auto KS_) {
+        constexpr int KS = decltype(KS_)::value;
+        hipLaunchKernelGGL((attn_bwd_small_dl_kernel<DH, KS>), dim3(2u * n_x * B * H), dim3(256 * KS), 0, s,
+                           static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o),
+                           static_cast<const bf16_t*>(dout), lse, delta, static_cast<bf16_t*>(dqkv), n_x, B * H, Tn, H);
+      };
+      if (split_bwd(B, Tn, H)) launch(std::integral_constant<int, 2>{});
+      else launch(std::integral_constant<int, 1>{});
       return hipGetLastError();
     }
     // dQ first: it computes D

@@ -341,15 +341,20 @@ def test_attention_fwd_bwd(dtype, B, T, H, dh):
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("T", [1, 63, 64, 65, 128, 129, 333, 2048, 2049])
 def test_attention_small_and_large_problems_agree(T, dh):
-    """A few heads take workgroups of 64 rows and one backward launch, many take
-    128 rows and two launches (as does the backward beyond 2048 rows); a head's
-    arithmetic is the same in both, so its results are the same bits."""
+    """Few heads take workgroups of 64 rows and one backward launch, many take 128
+    rows and two launches (as does the backward beyond 2048 rows); a head's
+    arithmetic is the same in both, so its results are the same bits.  Very few
+    heads of more than 256 rows also split the tiles between two groups of
+    waves: fp32 sums in another order and another reference maximum, so P and
+    dS round differently to bf16 (2^-9 each, before the outputs' own 2^-9)."""
     H = 4
-    copies = 1280 // (H * ((T + 63) // 64)) + 1  # past every small rule
+    n64 = H * ((T + 63) // 64)
+    middle = (256 if dh == 128 else 512) // n64 + 1  # past the split rules
+    copies = 1280 // n64 + 1                         # past every small rule
     d = H * dh
     qkv, do = attn_inputs(1, T, H, dh, "bf16", seed=T + dh)
     outs = []
-    for B in (1, copies):
+    for B in (1, middle, copies):
         dq, ddo = U.dev(qkv, "bf16").repeat(B, 1), U.dev(do, "bf16").repeat(B, 1)
         o, lse, delta = U.empty((B * T, d), "bf16"), U.empty((B, H, T), "f32"), U.empty((B, H, T), "f32")
         dqkv = U.empty((B * T, 3 * d), "bf16")
@@ -358,8 +363,12 @@ def test_attention_small_and_large_problems_agree(T, dh):
                           B, T, H, dh, stream())
         U.sync()
         outs.append([x.reshape(B, -1) for x in (o, lse, delta, dqkv)])
-    for small, large in zip(*outs):
-        assert (small == large).all()
+    for few, some, many in zip(*outs):
+        assert (some == some[:1]).all() and (many == some[:1]).all()
+        if T <= 256:
+            assert (few == many[:1]).all()
+        else:
+            assert U.rel_err(U.host(few[0]), U.host(many[0])) < 2.0**-8
 
 
 # ------------------------------------------------------- cross-entropy etc.
