@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(64 * NW * KS, WPS)
   const bf16_t* kb = qb + d;
   const bf16_t* vb = qb + 2 * d;
   const int q0 = blk.x * BQ;
-  const int part = w / NW;  // split of the key tiles
+  const int part = KS > 1 ? w / NW : 0;  // split of the key tiles
   const int qw = q0 + (w - part * NW) * 16 * G;
   const float sc = LOG2E / sqrtf(static_cast<float>(DH));
 
@@ -508,7 +508,7 @@ __global__ void __launch_bounds__(64 * NW * KS, WPS)
   auto load_stage = [&](int st, int kt) {
 #pragma unroll
     for (int u = 0; u < KS; ++u)
-      if (kt + u < n_kt) load_tile(st * KS + u, (kt + u) * BT);
+      if (u == 0 || kt + u < n_kt) load_tile(st * KS + u, (kt + u) * BT);
   };
   load_stage(0, 0);
   for (int k0 = 0; k0 < n_kt; k0 += KS) {
@@ -520,7 +520,7 @@ __global__ void __launch_bounds__(64 * NW * KS, WPS)
     if (k0 + KS < n_kt) load_stage(cur ^ 1, k0 + KS);
     const uint8_t* ks = lds + (cur * KS + part) * F::STAGE;
     const uint8_t* vs = ks + F::TILE;
-    if (kt < n_kt && j0 <= qw + 16 * G - 1) {
+    if ((KS == 1 || kt < n_kt) && j0 <= qw + 16 * G - 1) {
       float p[G][4][4];
       float mloc[G];
 #pragma unroll
@@ -1046,7 +1046,7 @@ __device__ __forceinline__ void bwd_dkdv_dl(uint8_t* lds, float* d_own, const Bl
   const float* lse_b = lse + (static_cast<int64_t>(b) * H + h) * Tn;
   const float* del_b = delta + (static_cast<int64_t>(b) * H + h) * Tn;
   const int k0 = blk.x * BKEYS;
-  const int part = w / W;                // split of the query tiles
+  const int part = KS > 1 ? w / W : 0;   // split of the query tiles
   const int kw = k0 + (w - part * W) * 16;  // this wave's first key
   const int kj = kw + lr;                // this lane's key
   const float sc = LOG2E / sqrtf(static_cast<float>(DH));
@@ -1309,7 +1309,7 @@ __device__ __forceinline__ void bwd_dq_dl(uint8_t* lds, const BlockId blk, const
   const bf16_t* vb = qb + 2 * d;
   const bf16_t* ob = dout + static_cast<int64_t>(b) * Tn * d + h * DH;
   const int q0 = blk.x * BQ;
-  const int part = w / NW;  // split of the key tiles
+  const int part = KS > 1 ? w / NW : 0;  // split of the key tiles
   const int qw = q0 + (w - part * NW) * 16;
   const int qi = qw + lr;
   const float sc = LOG2E / sqrtf(static_cast<float>(DH));
