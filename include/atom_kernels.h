@@ -41,7 +41,8 @@ enum {
  * count and an even leading dimension; A, B, C 16-byte aligned.
  * ws (fp32, ws_bytes, 16-byte aligned, may be NULL) lets a problem with few
  * output tiles and a long k split k over workgroups for the store epilogues
- * (STORE, STORE_F32, ACC_F32); the partials are summed in a fixed order. */
+ * (STORE, STORE_F32, ACC_F32); the partials are summed in a fixed order.  The
+ * other epilogues neither read nor write it. */
 int atom_k_gemm(int dtype, int a_kcontig, int b_kcontig, int epi, int M, int N, int K, const void* A, int64_t lda,
                 const void* B, int64_t ldb, void* C, int64_t ldc, const void* bias, const float* resid, void* aux,
                 int64_t ldaux, float* ws, uint64_t ws_bytes, void* stream);

@@ -40,8 +40,12 @@ int atom_k_gemm(int dtype, int a_kcontig, int b_kcontig, int epi, int M, int N, 
   g.M = M;
   g.N = N;
   g.K = K;
-  g.ws = ws;
-  g.ws_bytes = ws ? ws_bytes : 0;
+  // The workspace serves the store epilogues only: a caller may hand the same
+  // one to products with other epilogues on other streams.  (The step's own
+  // workspace, used on one stream, splits k before every epilogue.)
+  const bool store = epi == ATOM_EPI_STORE || epi == ATOM_EPI_STORE_F32 || epi == ATOM_EPI_ACC_F32;
+  g.ws = store ? ws : nullptr;
+  g.ws_bytes = g.ws ? ws_bytes : 0;
   return st(gemm(g, dtype, a_kcontig != 0, b_kcontig != 0, epi, S(stream)));
 }
 

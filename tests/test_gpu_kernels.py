@@ -224,13 +224,32 @@ def test_gemm_direct_load_edges(dtype, M, N, K):
 @pytest.mark.parametrize("M,N,K,ws", [
     (4008, 3064, 520, 0),  # 256x192 tiles, ragged rows, k ends inside a group of 128
     (1000, 8192, 2056, 0),  # 256x128 tiles, likewise
-    (136, 392, 8200, 64 << 20),  # splits of k, the last one short, before every epilogue
+    (136, 392, 8200, 64 << 20),  # splits of k, the last one short (store epilogues)
 ])
 @pytest.mark.parametrize("epi", ALL_EPI)
 def test_gemm_direct_load_tiles(akc, bkc, M, N, K, ws, epi):
     """Tile shapes and splits that the other sizes here do not reach; tolerances as
     for the pipelined path (one bf16 rounding, or fp32 sums of exact products)."""
     check_pipelined(akc, bkc, epi, M, N, K, seed=300 + akc + 2 * bkc + 4 * epi + K, ws_bytes=ws)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("epi", ALL_EPI)
+@pytest.mark.parametrize("N", [392, 390])  # the direct-load and the register-staged kernel
+def test_gemm_workspace_is_for_store_epilogues(dtype, epi, N):
+    """The workspace contract: the three store epilogues split a long k over it, the
+    others leave it as it is (a caller may share it with another stream then)."""
+    M, K = 136, 8192
+    a, b = U.dev(np.ones((M, K)), dtype), U.dev(np.ones((N, K)), dtype)
+    c, aux, res = U.empty((M, N), "f32"), U.dev(np.zeros((M, N)), dtype), U.dev_f32(np.zeros((M, N), np.float32))
+    bias = U.dev(np.zeros(N), dtype)
+    c.zero_()
+    ws = U.dev_f32(np.full(16 * M * N, 7.0, np.float32))
+    A.atom_k_gemm(U.dt_code(dtype), 1, 1, epi, M, N, K, U.ptr(a), K, U.ptr(b), K, U.ptr(c), N, U.ptr(bias), U.ptr(res),
+                  U.ptr(aux), N, stream(), ws=U.ptr(ws), ws_bytes=16 * M * N * 4)
+    U.sync()
+    store = epi in (A.ATOM_EPI_STORE, A.ATOM_EPI_STORE_F32, A.ATOM_EPI_ACC_F32)
+    assert bool((ws == 7.0).all()) == (not store)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
