@@ -453,6 +453,33 @@ def test_colsum(dtype):
         assert U.rel_err(U.host(out), x.astype(np.float64).sum(axis=0)) < 1e-5
 
 
+def chain_sum(rows):
+    """fp32 sum of the given rows, one after the other."""
+    s = np.zeros_like(rows[0])
+    for r in rows:
+        s = s + r
+    return s
+
+
+@pytest.mark.parametrize("cols", [256, 4096, 4100, 20480])
+@pytest.mark.parametrize("rows", [1, 16, 64, 65, 100, 520, 1024, 1025])
+def test_colsum_rounding(rows, cols):
+    """Up to 1024 rows the sum is one launch; its error against 64 bits is no larger
+    than that of the order beyond (partials of 16 rows, summed in 16 slices),
+    computed here in fp32.  Both are norms of `cols` independent errors, whose
+    ratio has a standard deviation of 1 / sqrt(cols): three of them."""
+    x = U.rng(rows + cols).standard_normal((rows, cols)).astype(np.float32)
+    ref = x.astype(np.float64).sum(axis=0)
+    parts = [chain_sum(x[i:i + 16]) for i in range(0, rows, 16)]
+    two = chain_sum([chain_sum(parts[i::16]) for i in range(min(16, len(parts)))])
+    dx, out = U.dev_f32(x), U.empty(cols, "f32")
+    part = U.empty(A.atom_k_colsum_part_floats(rows, cols), "f32")
+    A.atom_k_colsum(A.ATOM_F32, U.ptr(dx), rows, cols, U.ptr(out), U.ptr(part), stream())
+    U.sync()
+    err = np.linalg.norm(U.host(out) - ref)
+    assert err <= (1 + 3 / np.sqrt(cols)) * np.linalg.norm(two.astype(np.float64) - ref)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_embedding_forward(dtype):
     r = U.rng(4)
