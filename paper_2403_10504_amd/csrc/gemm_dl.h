@@ -259,16 +259,21 @@ gemm_dl_kernel(GemmArgs g) {
   };
 
   f32x4_t acc[TM][TN];
-  // fp32: odd k tiles have accumulators of their own, so that a sum has half
-  // as many roundings in a row (k = 1024: 256 MFMAs of 4)
-  constexpr bool TWO = sizeof(T) == 4;
-  f32x4_t acc2[TWO ? TM : 1][TWO ? TN : 1];
+  // fp32: odd k tiles have accumulators of their own, and after 512 k both join
+  // the running totals and start again from zero, so a sum has 64 MFMAs
+  // of 4 k in a row, and k / 512 totals, instead of k / 4.  Error against 64 bits at k =
+  // 8192: 3.0e-7 relative; 1.15e-6 without the totals, 8.1e-7 with the ranges
+  // that the register-staged kernel splits such a k into.  (One set of
+  // accumulators and totals after every 256 k: as exact, but the chain of
+  // MFMAs on one accumulator costs 3-4 % at 32x32.)
+  constexpr bool TOTALS = sizeof(T) == 4;
+  f32x4_t acc2[TOTALS ? TM : 1][TOTALS ? TN : 1], tot[TOTALS ? TM : 1][TOTALS ? TN : 1];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      if constexpr (TWO) acc2[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if constexpr (TOTALS) tot[i][j] = acc2[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       if constexpr (PIN) asm volatile("" : "+a"(acc[i][j]));
     }
   // wait states between the zeroing writes and the first MFMA reading them
@@ -328,7 +333,7 @@ gemm_dl_kernel(GemmArgs g) {
             if (l * TM / LT == i) load(S, kt, l);
         }
         if constexpr (PIN) mfma_agpr(acc[i][j], cb[j], ca[i]);
-        else if constexpr (TWO && (S & 1)) mfma16(acc2[i][j], cb[j], ca[i]);
+        else if constexpr (TOTALS && (S & 1)) mfma16(acc2[i][j], cb[j], ca[i]);
         else mfma16(acc[i][j], cb[j], ca[i]);
       }
     }
@@ -339,6 +344,16 @@ gemm_dl_kernel(GemmArgs g) {
     body(std::integral_constant<int, 1>{}, t + 1, fa1, fb1, fa0, fb0);
     body(std::integral_constant<int, 2>{}, t + 2, fa0, fb0, fa1, fb1);
     body(std::integral_constant<int, 3>{}, t + 3, fa1, fb1, fa0, fb0);
+    if constexpr (TOTALS)
+      if ((t & 12) == 12) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            tot[i][j] += acc[i][j] + acc2[i][j];
+            acc[i][j] = acc2[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          }
+      }
   }
 
   // every direct load has landed; wait states between the last MFMAs and
@@ -350,11 +365,11 @@ gemm_dl_kernel(GemmArgs g) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
   }
-  if constexpr (TWO) {
+  if constexpr (TOTALS) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] += acc2[i][j];
+      for (int j = 0; j < TN; ++j) acc[i][j] = tot[i][j] + (acc[i][j] + acc2[i][j]);
   }
   // Epilogue through LDS, RB rows of the wave's block at a time: the
   // accumulators go to a wave-private [RB][BN/2] fp32 staging area, and each

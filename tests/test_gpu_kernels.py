@@ -265,6 +265,26 @@ def test_gemm_split_k_is_exact_and_deterministic(dtype):
     assert not np.array_equal(c0, c1)  # the split path really ran (different summation order)
 
 
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("M,N,K", [(512, 1024, 8192), (1000, 2048, 4104), (96, 160, 16384), (64, 64, 512)])
+def test_gemm_f32_rounding(akc, bkc, M, N, K):
+    """fp32 sums take 256 products in a row (64 MFMAs of four in each of the two
+    sets) before they join the totals, K / 512 of those: with each addition
+    rounded by a uniform error of at most 2^-24 of the running sum, whose square
+    grows evenly, the relative error is at most 2^-24 sqrt((256 + K / 512) / 6)."""
+    r = U.rng(M + K)
+    Am = r.standard_normal((M, K) if akc else (K, M)).astype(np.float32)
+    Bm = r.standard_normal((N, K) if bkc else (K, N)).astype(np.float32)
+    dA, dB, dC = U.dev_f32(Am), U.dev_f32(Bm), U.empty((M, N), "f32")
+    A.atom_k_gemm(A.ATOM_F32, akc, bkc, A.ATOM_EPI_STORE, M, N, K, U.ptr(dA), Am.shape[1], U.ptr(dB), Bm.shape[1],
+                  U.ptr(dC), N, stream=stream())
+    U.sync()
+    pick = np.sort(r.choice(M, min(M, 64), replace=False))
+    ref = (Am if akc else Am.T)[pick].astype(np.float64) @ (Bm.T if bkc else Bm).astype(np.float64)
+    err = np.linalg.norm(U.host(dC)[pick] - ref) / np.linalg.norm(ref)
+    assert err <= 2.0**-24 * np.sqrt((256 + K / 512) / 6), err
+
+
 def test_gemm_rejects_unsupported_shapes():
     t = U.empty((64, 64), "bf16")
     with pytest.raises(A.AtomError):  # K not a multiple of 8
