@@ -27,7 +27,8 @@
 // Rows past the operand are clamped to its last valid row (or chunk of rows):
 // they only reach output rows or columns that are never stored.  k past the
 // end reads 16 bytes of zeros instead, in both operands, so any k whose
-// chunks are whole works; the loop runs whole groups of four k tiles.
+// chunks are whole works; the loop runs whole groups of four k tiles, then the
+// one to three that are left.
 #pragma once
 
 #include <algorithm>
@@ -196,9 +197,10 @@ constexpr int occupancy() {
   return lds > 80 * 1024 ? 1 : lds > 53 * 1024 ? 2 : lds > 40 * 1024 ? 3 : 4;
 }
 
-// TAIL: k is not a multiple of 128, so the last group of four k tiles reaches
-// past it and every load tests its chunk (three vector instructions: 3-4 % at
-// 4096x12288x4096, so whole groups take the copy without).
+// TAIL: k is not a multiple of 128, so one to three k tiles may follow the last
+// whole group of four, the last tile may reach past k, and every load tests its
+// chunk (three vector instructions: 3-4 % at 4096x12288x4096, so whole groups
+// take the copy without).
 template <typename T, bool AKC, bool BKC, int EPI, int BM, int BN, bool TAIL>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(occupancy<T, BM, BN>(), occupancy<T, BM, BN>())))
 gemm_dl_kernel(GemmArgs g) {
@@ -241,10 +243,12 @@ gemm_dl_kernel(GemmArgs g) {
 #pragma unroll
   for (int q = 0; q < OB::LPT; ++q) srb[q].init(static_cast<const T*>(g.B), g.ldb, n0, g.N, q * NT + tid);
   // k tiles of this workgroup: kquads groups of four per split, the rest in
-  // the last one (the launcher leaves none empty)
+  // the last one (the launcher leaves none empty).  With TAIL the last group
+  // may be short: only the tiles that hold k are loaded and multiplied.
   const int quads = (g.K + 4 * BK - 1) / (4 * BK);
   const int kbase = split * g.kquads * 4;
-  const int nk = min(g.kquads, quads - split * g.kquads) * 4;
+  const int nk4 = min(g.kquads, quads - split * g.kquads) * 4;
+  const int nk = TAIL ? min(nk4, (g.K + BK - 1) / BK - kbase) : nk4;
   // Each XCD starts its k loop at its own eighth of the range (the tile's
   // sum is rotated, the same for every launch of the shape).  Workgroups
   // walk k in step, so without it the whole GPU reads the same column range
@@ -252,7 +256,7 @@ gemm_dl_kernel(GemmArgs g) {
   // k are 32 KB apart and those addresses share their low bits, which crowds
   // a few memory channels (4096x4096x16384: 500 -> 418 us).  The workgroups
   // of one XCD share operand tiles through its L2, so they keep one offset.
-  const int koff = (xcd * (nk >> 3)) & ~3;
+  const int koff = (xcd * (nk4 >> 3)) & ~3;
   auto rot = [&](int kt) {
     const int r = kt + koff;
     return kbase + (r >= nk ? r - nk : r);
@@ -299,7 +303,7 @@ gemm_dl_kernel(GemmArgs g) {
   // iteration has the same loads outstanding; they land before the exit.
 #pragma unroll
   for (int s = 0; s < STAGES; ++s) {
-    const int kt = rot(s);
+    const int kt = rot(TAIL ? min(s, nk - 1) : s);
 #pragma unroll
     for (int l = 0; l < LT; ++l) load(s, kt, l);
   }
@@ -338,8 +342,8 @@ gemm_dl_kernel(GemmArgs g) {
       }
     }
   };
-  // nk is a multiple of 4: no tile is conditional inside the loop
-  for (int t = 0; t < nk; t += 4) {
+  // whole groups of four: no tile is conditional inside the loop
+  for (int t = 0; t + 4 <= nk; t += 4) {
     body(std::integral_constant<int, 0>{}, t, fa0, fb0, fa1, fb1);
     body(std::integral_constant<int, 1>{}, t + 1, fa1, fb1, fa0, fb0);
     body(std::integral_constant<int, 2>{}, t + 2, fa0, fb0, fa1, fb1);
@@ -354,6 +358,13 @@ gemm_dl_kernel(GemmArgs g) {
             acc[i][j] = acc2[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
           }
       }
+  }
+
+  if constexpr (TAIL) {
+    const int t = nk & ~3;
+    if (t < nk) body(std::integral_constant<int, 0>{}, t, fa0, fb0, fa1, fb1);
+    if (t + 1 < nk) body(std::integral_constant<int, 1>{}, t + 1, fa1, fb1, fa0, fb0);
+    if (t + 2 < nk) body(std::integral_constant<int, 2>{}, t + 2, fa0, fb0, fa1, fb1);
   }
 
   // every direct load has landed; wait states between the last MFMAs and

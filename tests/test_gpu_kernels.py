@@ -233,6 +233,16 @@ def test_gemm_direct_load_tiles(akc, bkc, M, N, K, ws, epi):
     check_pipelined(akc, bkc, epi, M, N, K, seed=300 + akc + 2 * bkc + 4 * epi + K, ws_bytes=ws)
 
 
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("K", [8, 32, 40, 64, 96, 104, 160, 200, 224])
+def test_gemm_k_tail(akc, bkc, K):
+    """One to four k tiles of 32, and one to three after a whole group of four, the
+    last one whole or not: only the tiles that hold k are loaded and multiplied."""
+    for dtype, M, N in (("bf16", 264, 200), ("bf16", 2808, 1224), ("f32", 68, 100)):
+        err, tol = gemm_case(dtype, akc, bkc, M, N, K, A.ATOM_EPI_STORE, seed=M + K + akc + 2 * bkc)
+        assert err < tol, (dtype, M, err)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("epi", ALL_EPI)
 @pytest.mark.parametrize("N", [392, 390])  # the direct-load and the register-staged kernel
