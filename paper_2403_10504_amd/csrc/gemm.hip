@@ -508,12 +508,22 @@ Choice choose(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
   return best;
 }
 
+// Whether the direct-load kernel stores an fp32 result past the caches: it
+// overflows them (STREAM_BYTES; logits of a head chunk), and its rows are whole
+// 128-byte lines.  Other rows share lines with their neighbours, which cached
+// stores merge (fp32 12400 x 5496 with k = 128: 65 us cached, 84 streamed;
+// 10144 x 9056: 86 and 84).
+bool stream_result(const GemmArgs& g, int epi, int splits) {
+  return epi == EPI_STORE_F32 && splits == 1 && g.ldc % 32 == 0 && static_cast<int64_t>(g.M) * g.N * 4 > STREAM_BYTES;
+}
+
 template <typename T>
 hipError_t launch_dl(GemmArgs g, bool akc, bool bkc, int epi, hipStream_t s) {
   const Choice c = choose(g, sizeof(T), akc, bkc, epi);
   const int quads = (g.K + 127) / 128;
   g.kquads = (quads + c.splits - 1) / c.splits;
   g.splits = (quads + g.kquads - 1) / g.kquads;  // none empty
+  g.stream = stream_result(g, epi, g.splits);
   GemmArgs k = g;
   const int kepi = g.splits > 1 ? EPI_STORE_F32 : epi;
   if (g.splits > 1) {
@@ -590,3 +600,20 @@ hipError_t gemm(const GemmArgs& g, int dtype, bool akc, bool bkc, int epi, hipSt
 }
 
 }  // namespace atom
+
+// What a product with contiguous operands and rows runs as (tests).
+extern "C" void atom_gemm_choice(int dtype, int akc, int bkc, int epi, int M, int N, int K, uint64_t ws_bytes,
+                                 int* out) {
+  using namespace atom;
+  GemmArgs g{};
+  g.M = M, g.N = N, g.K = K;
+  g.lda = akc ? K : M, g.ldb = bkc ? K : N, g.ldc = g.ldaux = N;
+  float some;
+  g.ws = ws_bytes ? &some : nullptr;
+  g.ws_bytes = ws_bytes;
+  const int esz = dtype == DT_BF16 ? 2 : 4;
+  const bool dl = dl_applies(g, esz, akc != 0, bkc != 0, epi);
+  const Choice c = dl ? choose(g, esz, akc != 0, bkc != 0, epi) : Choice{BM, BN, 1};
+  out[0] = !dl, out[1] = c.bm, out[2] = c.bn, out[3] = c.splits;
+  out[4] = dl && stream_result(g, epi, c.splits);
+}

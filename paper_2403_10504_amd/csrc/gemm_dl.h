@@ -403,8 +403,6 @@ gemm_dl_kernel(GemmArgs g) {
   float bv[4] = {0.f, 0.f, 0.f, 0.f};
   if constexpr (epi_has_bias<EPI>())
     if (col_ok) unpack4(static_cast<const T*>(g.bias) + nb, bv);
-  // fp32 logits of a head chunk (412 MB for 2048 x 50304)
-  const bool stream_out = EPI == EPI_STORE_F32 && g.splits == 1 && static_cast<int64_t>(g.M) * g.N * 4 > STREAM_BYTES;
   // The element operands (C itself, the fp32 residual or the saved
   // pre-activation) are requested ahead of their use: every CU reaches its
   // epilogue at about the same time, so a load issued just before its use
@@ -491,7 +489,7 @@ gemm_dl_kernel(GemmArgs g) {
           for (int r = 0; r < 4; ++r) v[r] *= gelu_grad_f(xe[r]);
         }
         if constexpr (E == EPI_STORE_F32) {
-          if (stream_out) stream4(static_cast<float*>(ga.C) + off, v);
+          if (g.stream) stream4(static_cast<float*>(ga.C) + off, v);
           else pack4(static_cast<float*>(ga.C) + off, v);
         } else if constexpr (F32_OUT) pack4(static_cast<float*>(ga.C) + off, v);
         else pack4(static_cast<T*>(ga.C) + off, v);

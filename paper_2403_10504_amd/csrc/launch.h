@@ -31,6 +31,7 @@ struct GemmArgs {
   float* ws;          // optional fp32 workspace for a split over k (may be null)
   uint64_t ws_bytes;  // its size; a split needs splits * M * N * 4 bytes
   int splits, kquads; // set by the launcher: k ranges and the groups of 128 k of each
+  bool stream;        // set by the launcher: fp32 results are stored past the caches
 };
 
 // The layout and epilogue combinations of the training step: forward, data

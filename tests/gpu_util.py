@@ -99,3 +99,17 @@ def host_digests(sess, which):
 
     with ThreadPoolExecutor(8) as ex:
         return list(ex.map(one, range(sess.n_nodes)))
+
+
+def gemm_choice(dtype, akc, bkc, epi, M, N, K, ws_bytes=0):
+    """What atom_k_gemm runs a product with contiguous operands as, by the library's own rule:
+    (register-staged, tile rows, tile columns, splits of k, result stored past the caches)."""
+    import ctypes
+
+    from paper_2403_10504_amd import atom as A
+
+    out = (ctypes.c_int * 5)()
+    f = A.lib().atom_gemm_choice
+    f.argtypes, f.restype = [ctypes.c_int] * 7 + [ctypes.c_uint64, ctypes.c_void_p], None
+    f(dt_code(dtype), akc, bkc, epi, M, N, K, ws_bytes, ctypes.addressof(out))
+    return tuple(out)

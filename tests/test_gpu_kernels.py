@@ -243,6 +243,16 @@ def test_gemm_k_tail(akc, bkc, K):
         assert err < tol, (dtype, M, err)
 
 
+@pytest.mark.parametrize("N", [5496, 5504])
+def test_gemm_large_result_rows(N):
+    """fp32 results of more than 256 MB: stored past the caches where their rows are
+    whole 128-byte lines (5504 columns), through them otherwise (5496)."""
+    M, K = 12400, 72
+    assert U.gemm_choice("bf16", 1, 1, A.ATOM_EPI_STORE_F32, M, N, K)[4] == (N % 32 == 0)
+    err, _ = sampled_gemm_check("bf16", 1, 1, M, N, K, seed=N)
+    assert err < 1e-4, err
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("epi", ALL_EPI)
 @pytest.mark.parametrize("N", [392, 390])  # the direct-load and the register-staged kernel
