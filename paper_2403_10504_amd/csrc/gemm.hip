@@ -10,10 +10,12 @@
 //   data grad dx = dy W   : A = dy (KC),          B = W  (not KC)
 //   weight grad dW = dy^T x: A = dy (not KC),      B = x  (not KC)
 //
-// The direct-load kernel (gemm_dl.h) takes every problem whose 16-byte chunks
-// are whole; choose() picks its tile and a split over k.  The kernel here is
-// for the rest (odd row counts or leading dimensions): 128x128 tiles of four
-// waves, a 128-byte k tile (64 bf16 or 32 fp32) staged through registers and
+// The direct-load kernel (gemm_dl.h) takes the problems whose 16-byte chunks
+// are whole (dl_applies); choose() picks its tile and a split over k.  The kernel here is for the rest (k, leading dimensions
+// or rows of a not k-contiguous operand that are no multiples of 8 in bf16 or 4
+// in fp32, N or ldc no multiples of 4): tiles of 128x128 by four waves or, of
+// large bf16 problems, 256x256 by sixteen, a 128-byte k tile (64 bf16 or 32
+// fp32) staged through registers and
 // double-buffered in LDS with k contiguous (rows padded to 144 bytes to
 // spread ds_read_b128 over the banks; operands that are not k-contiguous in
 // memory are transposed while being written to LDS).  A split over k writes
@@ -30,9 +32,15 @@ namespace {
 
 constexpr int ROW_BYTES = 128, PITCH_BYTES = 144;
 
-// Workgroup tile BM x BN computed by 2 x 2 waves, each owning a
-// (BM/2) x (BN/2) block of 16x16 MFMA tiles.
-constexpr int BM = 128, BN = 128, NT = 256, TM = BM / 32, TN = BN / 32;
+// Workgroup tile of BS x BS computed by W x W waves, each owning a 64 x 64
+// block of 16x16 MFMA tiles.
+template <int BS_>
+struct Cfg {
+  static constexpr int BS = BS_, W = BS / 64, NT = 64 * W * W;
+};
+using Small = Cfg<128>;
+using Big = Cfg<256>;
+constexpr int TM = 4, TN = 4;
 
 template <typename T>
 struct Tile {
@@ -243,16 +251,17 @@ __device__ __forceinline__ void epilogue4(const GemmArgs& g, int m, int nb, floa
 // One output tile per workgroup (blockIdx.x), one k range per split
 // (blockIdx.y).  With splits > 1 the raw fp32 sums go to the workspace
 // ws[split][M][N] and splitk_reduce applies the epilogue.
-template <typename T, bool AKC, bool BKC, int EPI>
-__global__ void __launch_bounds__(NT) gemm_kernel(GemmArgs g) {
+template <typename T, bool AKC, bool BKC, int EPI, class CF>
+__global__ void __launch_bounds__(CF::NT) gemm_kernel(GemmArgs g) {
   using TL = Tile<T>;
+  constexpr int BM = CF::BS, BN = CF::BS, NT = CF::NT;
   __shared__ __attribute__((aligned(16))) T As[2][BM * TL::PITCH];
   __shared__ __attribute__((aligned(16))) T Bs[2][BN * TL::PITCH];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const int wm = w >> 1, wn = w & 1;
+  const int wm = w / CF::W, wn = w % CF::W;
 
   // Tile order: XCD-aware remap (consecutive ids go round-robin over the 8
   // XCDs, so give each XCD a contiguous range), then groups of 8 row-tiles
@@ -396,6 +405,9 @@ __global__ void __launch_bounds__(256) splitk_reduce(GemmArgs g, int splits) {
   }
 }
 
+// Output tiles of bs x bs.
+int tiles_of(const GemmArgs& g, int bs) { return ((g.M + bs - 1) / bs) * ((g.N + bs - 1) / bs); }
+
 template <typename T>
 hipError_t launch_reduce(const GemmArgs& g, int epi, int splits, hipStream_t s) {
   const int64_t MN = static_cast<int64_t>(g.M) * g.N;
@@ -416,13 +428,12 @@ hipError_t launch_reduce(const GemmArgs& g, int epi, int splits, hipStream_t s) 
   return hipGetLastError();
 }
 
-template <typename T, bool AKC, bool BKC>
-hipError_t launch_small(const GemmArgs& g, int epi, int splits, hipStream_t s) {
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  dim3 grid(tiles, splits), block(NT);
+template <typename T, bool AKC, bool BKC, class CF>
+hipError_t launch_cfg(const GemmArgs& g, int epi, int splits, hipStream_t s) {
+  dim3 grid(tiles_of(g, CF::BS), splits), block(CF::NT);
   switch (epi) {
 #define ATOM_CASE(E) \
-  case E: hipLaunchKernelGGL((gemm_kernel<T, AKC, BKC, E>), grid, block, 0, s, g); break;
+  case E: hipLaunchKernelGGL((gemm_kernel<T, AKC, BKC, E, CF>), grid, block, 0, s, g); break;
     ATOM_CASE(EPI_STORE)
     ATOM_CASE(EPI_STORE_F32)
     ATOM_CASE(EPI_ACC_F32)
@@ -449,6 +460,13 @@ bool dl_applies(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
          g.N % 4 == 0 && g.ldc % 4 == 0 && (!aux || g.ldaux % 4 == 0);
 }
 
+// What a problem runs as: the direct-load kernel's tile and its split over k,
+// or (staged) the register-staged kernel's.
+struct Choice {
+  int bm, bn, splits;
+  bool staged;
+};
+
 // Tile configurations of the direct-load kernel with the times the choice
 // rests on, in us: a CU's time for one k tile (32) of one workgroup, and for
 // a workgroup's start and epilogue.  Fitted to 963 problems (the four
@@ -471,18 +489,13 @@ constexpr TileCfg F32_TILES[] = {{64, 64, 2, 0.60, 0.5}, {32, 32, 4, 0.165, 0.1}
 // A split over k: the second kernel's launch, and every partial written and
 // read once.
 constexpr double SPLIT_FIXED = 3.9, SPLIT_US_PER_PARTIAL = 1.34e-6;
-constexpr int MAX_SPLITS = 12;
-
-struct Choice {
-  int bm, bn, splits;
-};
+constexpr int MAX_SPLITS = 12, CUS = 256;
 
 // The configuration and split count with the smallest predicted time.
 Choice choose(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
-  constexpr int CUS = 256;
   const int quads = (g.K + 127) / 128;
   const double mn = static_cast<double>(g.M) * g.N;
-  Choice best{0, 0, 1};
+  Choice best{0, 0, 1, false};
   double best_t = 0.0;
   auto consider = [&](const TileCfg& c) {
     if (c.bm == 256 && c.bn < 256 && !gemm_main_combo(akc, bkc, epi)) return;
@@ -498,7 +511,7 @@ Choice choose(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
       double t = share * (4.0 * per * c.ktile + c.fixed);
       if (want > 1) t += SPLIT_FIXED + SPLIT_US_PER_PARTIAL * mn * want;
       if (best.bm == 0 || t < best_t) {
-        best = Choice{c.bm, c.bn, want};
+        best = Choice{c.bm, c.bn, want, false};
         best_t = t;
       }
     }
@@ -506,6 +519,37 @@ Choice choose(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
   if (esz == 2) for (const auto& c : BF16_TILES) consider(c);
   else for (const auto& c : F32_TILES) consider(c);
   return best;
+}
+
+// The register-staged kernel's choice: 128x128 tiles, split over k where those
+// leave the CUs idle and k is long, limited by the workspace; in bf16 256x256
+// tiles from one per CU on while a round of them (one per CU) takes less than
+// the rounds of 128x128 tiles (two per CU) it stands for.  A round takes 1.85
+// times as long at small k, towards 1.9, 1.45 and 1.27 times at large k with
+// two, one and no k-contiguous operand (transposing into LDS costs the 128x128
+// tile most).  1792 problems with t256 >= 256: 3428x8096x896 neither
+// k-contiguous 113 -> 79 us, 4096x50258x4096 both 2279 -> 1912; 15699x7318x128
+// 260 in 256x256, 248 in 128x128.
+Choice choose_staged(const GemmArgs& g, int esz, bool akc, bool bkc) {
+  const int t256 = tiles_of(g, 256), tiles = tiles_of(g, 128);
+  if (esz == 2 && t256 >= CUS) {
+    const double far = akc && bkc ? 1.9 : akc || bkc ? 1.45 : 1.27;
+    const double ratio = far + (1.85 - far) * 256 / (g.K + 256);
+    if ((t256 + CUS - 1) / CUS * ratio < (tiles + 2 * CUS - 1) / (2 * CUS)) return Choice{256, 256, 1, true};
+  }
+  const int bk = ROW_BYTES / esz, nk = (g.K + bk - 1) / bk;
+  int splits = 1;
+  if (g.ws && tiles < 2 * CUS && nk >= 32) {
+    splits = std::min((2 * CUS + tiles - 1) / tiles, nk / 16);
+    const int64_t per = static_cast<int64_t>(g.M) * g.N * 4;
+    splits = static_cast<int>(std::min<int64_t>(splits, static_cast<int64_t>(g.ws_bytes / per)));
+    splits = std::max(1, std::min(splits, 16));
+  }
+  return Choice{128, 128, splits, true};
+}
+
+Choice choice_of(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
+  return dl_applies(g, esz, akc, bkc, epi) ? choose(g, esz, akc, bkc, epi) : choose_staged(g, esz, akc, bkc);
 }
 
 // Whether the direct-load kernel stores an fp32 result past the caches: it
@@ -518,8 +562,7 @@ bool stream_result(const GemmArgs& g, int epi, int splits) {
 }
 
 template <typename T>
-hipError_t launch_dl(GemmArgs g, bool akc, bool bkc, int epi, hipStream_t s) {
-  const Choice c = choose(g, sizeof(T), akc, bkc, epi);
+hipError_t launch_dl(GemmArgs g, const Choice& c, bool akc, bool bkc, int epi, hipStream_t s) {
   const int quads = (g.K + 127) / 128;
   g.kquads = (quads + c.splits - 1) / c.splits;
   g.splits = (quads + g.kquads - 1) / g.kquads;  // none empty
@@ -543,22 +586,13 @@ hipError_t launch_dl(GemmArgs g, bool akc, bool bkc, int epi, hipStream_t s) {
   return launch_reduce<T>(g, epi, g.splits, s);
 }
 
-// Everything else: 128x128 tiles, split over k where those leave the CUs idle
-// and k is long, limited by the workspace.
 template <typename T, bool AKC, bool BKC>
 hipError_t launch_t(const GemmArgs& g, int epi, hipStream_t s) {
-  constexpr int CUS = 256;
-  if (dl_applies(g, sizeof(T), AKC, BKC, epi)) return launch_dl<T>(g, AKC, BKC, epi, s);
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  const int nk = (g.K + Tile<T>::BK - 1) / Tile<T>::BK;
-  int splits = 1;
-  if (g.ws && tiles < 2 * CUS && nk >= 32) {
-    splits = std::min((2 * CUS + tiles - 1) / tiles, nk / 16);
-    const int64_t per = static_cast<int64_t>(g.M) * g.N * 4;
-    splits = static_cast<int>(std::min<int64_t>(splits, static_cast<int64_t>(g.ws_bytes / per)));
-    splits = std::max(1, std::min(splits, 16));
-  }
-  return launch_small<T, AKC, BKC>(g, epi, splits, s);
+  const Choice c = choice_of(g, sizeof(T), AKC, BKC, epi);
+  if (!c.staged) return launch_dl<T>(g, c, AKC, BKC, epi, s);
+  if constexpr (sizeof(T) == 2)
+    if (c.bm == 256) return launch_cfg<T, AKC, BKC, Big>(g, epi, 1, s);
+  return launch_cfg<T, AKC, BKC, Small>(g, epi, c.splits, s);
 }
 
 }  // namespace
@@ -611,9 +645,7 @@ extern "C" void atom_gemm_choice(int dtype, int akc, int bkc, int epi, int M, in
   float some;
   g.ws = ws_bytes ? &some : nullptr;
   g.ws_bytes = ws_bytes;
-  const int esz = dtype == DT_BF16 ? 2 : 4;
-  const bool dl = dl_applies(g, esz, akc != 0, bkc != 0, epi);
-  const Choice c = dl ? choose(g, esz, akc != 0, bkc != 0, epi) : Choice{BM, BN, 1};
-  out[0] = !dl, out[1] = c.bm, out[2] = c.bn, out[3] = c.splits;
-  out[4] = dl && stream_result(g, epi, c.splits);
+  const Choice c = choice_of(g, dtype == DT_BF16 ? 2 : 4, akc != 0, bkc != 0, epi);
+  out[0] = c.staged, out[1] = c.bm, out[2] = c.bn, out[3] = c.splits;
+  out[4] = !c.staged && stream_result(g, epi, c.splits);
 }

@@ -243,6 +243,17 @@ def test_gemm_k_tail(akc, bkc, K):
         assert err < tol, (dtype, M, err)
 
 
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0)])
+@pytest.mark.parametrize("epi", ALL_EPI)
+def test_gemm_unaligned_large(akc, bkc, epi):
+    """bf16 rows that are no whole 16-byte chunks (k-contiguous operands: no whole
+    output 4-vectors), in numbers for which the register-staged kernel takes 256x256
+    tiles: ragged in rows, columns and k."""
+    M, N, K = 3428, 8094, 456
+    assert U.gemm_choice("bf16", akc, bkc, epi, M, N, K) == (1, 256, 256, 1, 0)
+    check_pipelined(akc, bkc, epi, M, N, K, seed=600 + akc + 2 * bkc + 4 * epi)
+
+
 @pytest.mark.parametrize("N", [5496, 5504])
 def test_gemm_large_result_rows(N):
     """fp32 results of more than 256 MB: stored past the caches where their rows are
