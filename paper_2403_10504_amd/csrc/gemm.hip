@@ -11,7 +11,8 @@
 //   weight grad dW = dy^T x: A = dy (not KC),      B = x  (not KC)
 //
 // The direct-load kernel (gemm_dl.h) takes the problems whose 16-byte chunks
-// are whole (dl_applies); choose() picks its tile and a split over k.  The kernel here is for the rest (k, leading dimensions
+// are whole (dl_applies), but for fp32 ones of short k; choose() picks its tile
+// and a split over k.  The kernel here is for the rest (k, leading dimensions
 // or rows of a not k-contiguous operand that are no multiples of 8 in bf16 or 4
 // in fp32, N or ldc no multiples of 4): tiles of 128x128 by four waves or, of
 // large bf16 problems, 256x256 by sixteen, a 128-byte k tile (64 bf16 or 32
@@ -467,57 +468,84 @@ struct Choice {
   bool staged;
 };
 
-// Tile configurations of the direct-load kernel with the times the choice
-// rests on, in us: a CU's time for one k tile (32) of one workgroup, and for
-// a workgroup's start and epilogue.  Fitted to 963 problems (the four
-// configurations' layers, short and ragged token counts, vocabularies) x
-// every tile and split that fits, on one machine, for the smallest loss
-// against the best of them: 1.6 % on average.  What they say: big tiles read
-// the least per FLOP, 192 or 128 columns where 256 divide N badly
-// (16384x768x3072: 78 -> 75 us; 2048x5120x15360: 310 -> 273; 1000x8192x2048:
-// 54 -> 40), 128x128 and 64x64 where there are too few big tiles for 256 CUs
-// (1000x2048x8192: 157 -> 61, 44 split in two; 520x768x3072: 65 -> 17).
+// Tile configurations with the times the choice rests on, in us: a CU's time
+// for one k tile (32) of one workgroup, for a workgroup's start and its
+// epilogue (to the element type; epi: what fp32 stores, fp32 read and written,
+// GELU forward and GELU backward take more), and once per call.  Fitted to
+// 18686 problems in bf16 and 11450 in fp32 (sizes 64 to 16384, every layout
+// and epilogue) x every tile and split that fits, on one machine, for the
+// smallest loss against the best of them, above all where a single 256x256 or
+// register-staged 128x128 tile would win: 0.8 and 0.5 % on average (with no
+// epilogue terms 2 and 1.8 %, short k lost most: 14824x12136x384 187 us in
+// 256x256 tiles, 234 in 128x128).  What they say: big tiles read the least per
+// FLOP, 192 or 128 columns where 256 divide N badly (16384x768x3072: 78 -> 75
+// us; 2048x5120x15360: 310 -> 273; 1000x8192x2048: 54 -> 40), 128x128 and 64x64
+// where there are too few big tiles for 256 CUs (1000x2048x8192: 157 -> 61, 44
+// split in two; 520x768x3072: 65 -> 17).
 struct TileCfg {
   int bm, bn, occ;  // occ: workgroups a CU holds
-  double ktile, fixed;
+  double ktile, fixed, epi[4], call;
 };
-constexpr TileCfg BF16_TILES[] = {
-    {256, 256, 1, 0.745, 7.2}, {256, 192, 1, 0.607, 5.5}, {256, 128, 1, 0.451, 4.2}, {128, 128, 2, 0.279, 0.43}, {64, 64, 4, 0.142, 0.0}};
-// fp32: the matrix cores bound both (512 and 128 MFMAs of 32 cycles per k
-// tile); 64x64 is 5-10 % faster where it fills the chip.
-constexpr TileCfg F32_TILES[] = {{64, 64, 2, 0.60, 0.5}, {32, 32, 4, 0.165, 0.1}};
-// A split over k: the second kernel's launch, and every partial written and
-// read once.
-constexpr double SPLIT_FIXED = 3.9, SPLIT_US_PER_PARTIAL = 1.34e-6;
-constexpr int MAX_SPLITS = 12, CUS = 256;
+constexpr TileCfg BF16_TILES[] = {{256, 256, 1, 0.604, 8.93, {3.26, 10.96, 7.39, 18.10}, 0.70},
+                                  {256, 192, 1, 0.486, 7.82, {1.66, 7.20, 8.13, 13.97}, 1.89},
+                                  {256, 128, 1, 0.412, 5.52, {1.34, 5.36, 4.31, 6.24}, 0.80},
+                                  {128, 128, 2, 0.249, 1.74, {0.63, 2.11, 1.82, 2.08}, 2.10},
+                                  {64, 64, 4, 0.131, 0.437, {0.255, 0.358, 0.373, 0.371}, 1.58}};
+// fp32: the matrix cores bound both direct-load tiles (512 and 128 MFMAs of 32
+// cycles per k tile); 64x64 is 5-10 % faster where it fills the chip.  The
+// register-staged 128x128 tile up to 256 k, where stores and starts dominate
+// (5020x1524x136: 44 -> 30 us; from there on it loses, and its one set of
+// accumulators sums more than 64 MFMAs in a row).
+constexpr TileCfg F32_TILES[] = {{64, 64, 2, 0.554, 1.138, {0.034, 0.195, 0.316, 0.443}, 2.93},
+                                 {32, 32, 4, 0.157, 0.353, {0.023, 0.048, 0.08, 0.169}, 2.90}};
+constexpr TileCfg F32_STAGED = {128, 128, 2, 2.258, 3.0, {-0.13, 3.88, 4.12, 6.15}, 5.12};
+constexpr int STAGED_MAX_K = 256;
+// A split over k: the second kernel's launch, every partial written and read
+// once, its epilogue as above, and per range.
+struct SplitCost {
+  double fixed, per_partial, epi[3], range;
+};
+constexpr SplitCost BF16_SPLIT = {2.86, 0.661e-6, {0.694e-6, 1.491e-6, 1.041e-6}, 0.315};
+constexpr SplitCost F32_SPLIT = {2.1, 0.257e-6, {1.404e-6, 1.689e-6, 3.692e-6}, 0.0};
+constexpr int MAX_SPLITS = 16, CUS = 256;
 
 // The configuration and split count with the smallest predicted time.
 Choice choose(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
   const int quads = (g.K + 127) / 128;
   const double mn = static_cast<double>(g.M) * g.N;
+  const SplitCost& sc = esz == 2 ? BF16_SPLIT : F32_SPLIT;
+  // index into epi[], -1: to the element type
+  const int e = epi == EPI_STORE_F32 ? 0 : epi == EPI_ACC_F32 || epi == EPI_BIAS_RESID ? 1 : epi == EPI_BIAS_GELU ? 2
+              : epi == EPI_GELU_BWD ? 3 : -1;
   Choice best{0, 0, 1, false};
   double best_t = 0.0;
-  auto consider = [&](const TileCfg& c) {
+  auto consider = [&](const TileCfg& c, bool staged) {
     if (c.bm == 256 && c.bn < 256 && !gemm_main_combo(akc, bkc, epi)) return;
     const int64_t tiles = static_cast<int64_t>((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
-    for (int want = 1; want <= MAX_SPLITS; ++want) {
+    for (int want = 1; want <= (staged ? 1 : MAX_SPLITS); ++want) {
       const int per = (quads + want - 1) / want, splits = (quads + per - 1) / per;
       if (splits != want) continue;
+      if (want > 1 && (!g.ws || mn * want * 4 > static_cast<double>(g.ws_bytes))) break;
       // two groups of 128 k per range at least, and no more ranges than fill the chip twice
-      if (want > 1 && (per < 2 || tiles * want > 2 * CUS * c.occ || !g.ws || mn * want * 4 > static_cast<double>(g.ws_bytes)))
-        break;
+      if (want > 1 && (per < 2 || tiles * want > 2 * CUS * c.occ)) break;
       // the most workgroups a CU gets
       const double share = static_cast<double>((tiles * want + CUS - 1) / CUS);
-      double t = share * (4.0 * per * c.ktile + c.fixed);
-      if (want > 1) t += SPLIT_FIXED + SPLIT_US_PER_PARTIAL * mn * want;
+      const int ktiles = want > 1 ? 4 * per : (g.K + 31) / 32, ke = want > 1 ? 0 : e;
+      double t = share * (ktiles * c.ktile + c.fixed + (ke >= 0 ? c.epi[ke] : 0.0)) + c.call;
+      if (want > 1)
+        t += sc.fixed + mn * (sc.per_partial * want + (e > 0 ? sc.epi[e - 1] : 0.0)) + sc.range * want;
       if (best.bm == 0 || t < best_t) {
-        best = Choice{c.bm, c.bn, want, false};
+        best = Choice{c.bm, c.bn, want, staged};
         best_t = t;
       }
     }
   };
-  if (esz == 2) for (const auto& c : BF16_TILES) consider(c);
-  else for (const auto& c : F32_TILES) consider(c);
+  if (esz == 2) {
+    for (const auto& c : BF16_TILES) consider(c, false);
+  } else {
+    for (const auto& c : F32_TILES) consider(c, false);
+    if (g.K <= STAGED_MAX_K) consider(F32_STAGED, true);
+  }
   return best;
 }
 

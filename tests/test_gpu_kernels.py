@@ -243,6 +243,21 @@ def test_gemm_k_tail(akc, bkc, K):
         assert err < tol, (dtype, M, err)
 
 
+def test_gemm_choice_of_short_k():
+    """Where starts, epilogues and stores dominate, big tiles stay ahead of 128x128 ones."""
+    for akc, bkc, epi, M, N, K in ((1, 0, A.ATOM_EPI_STORE, 14824, 12136, 384), (1, 1, A.ATOM_EPI_BIAS, 7080, 16144, 384)):
+        assert U.gemm_choice("bf16", akc, bkc, epi, M, N, K)[1] == 256, (M, N, K)
+
+
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
+def test_gemm_f32_short_k(akc, bkc):
+    """fp32 problems of many tiles and at most 256 k take the register-staged kernel."""
+    M, N, K = 1548, 4588, 72
+    assert U.gemm_choice("f32", akc, bkc, A.ATOM_EPI_STORE, M, N, K)[:4] == (1, 128, 128, 1)
+    err, tol = gemm_case("f32", akc, bkc, M, N, K, A.ATOM_EPI_STORE, seed=K + akc + 2 * bkc)
+    assert err < tol, err
+
+
 @pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0)])
 @pytest.mark.parametrize("epi", ALL_EPI)
 def test_gemm_unaligned_large(akc, bkc, epi):
