@@ -509,9 +509,28 @@ constexpr SplitCost BF16_SPLIT = {2.86, 0.661e-6, {0.694e-6, 1.491e-6, 1.041e-6}
 constexpr SplitCost F32_SPLIT = {2.1, 0.257e-6, {1.404e-6, 1.689e-6, 3.692e-6}, 0.0};
 constexpr int MAX_SPLITS = 16, CUS = 256;
 
+// Ranges of k that an fp32 result of bf16 operands is at least the sum of, so
+// that its rounding error stays that of 256-row tiles split until 192
+// workgroups run, or of 128-row tiles split into ranges of 1024 k (a sum takes
+// k / 32 MFMAs in a row: 1.5e-7 relative at 512 k and 3.1e-7 at 2560).  Other
+// results round to bf16, 1.7e-3.
+int min_ranges(const GemmArgs& g, int esz, int epi) {
+  if (esz != 2 || !g.ws || (epi != EPI_STORE_F32 && epi != EPI_ACC_F32)) return 1;
+  const int t256 = tiles_of(g, 256), t128 = tiles_of(g, 128);
+  if (t256 >= 192) return 1;
+  const int64_t held = static_cast<int64_t>(g.ws_bytes) / (static_cast<int64_t>(g.M) * g.N * 4);
+  const int most = static_cast<int>(std::min<int64_t>(held, MAX_SPLITS));
+  int n = 1;
+  const bool whole = (g.M | g.N) % 8 == 0;
+  while (whole && 2 * n <= most && t256 * n < 192 && g.K % (256 * n) == 0) n *= 2;
+  if (n > 1 && t256 * n >= 96) return n;
+  if (t128 >= 2 * CUS || g.K < 2048) return 1;
+  return std::max(1, std::min({(2 * CUS + t128 - 1) / t128, g.K / 1024, most}));
+}
+
 // The configuration and split count with the smallest predicted time.
 Choice choose(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
-  const int quads = (g.K + 127) / 128;
+  const int quads = (g.K + 127) / 128, least = min_ranges(g, esz, epi);
   const double mn = static_cast<double>(g.M) * g.N;
   const SplitCost& sc = esz == 2 ? BF16_SPLIT : F32_SPLIT;
   // index into epi[], -1: to the element type
@@ -527,13 +546,14 @@ Choice choose(const GemmArgs& g, int esz, bool akc, bool bkc, int epi) {
       if (splits != want) continue;
       if (want > 1 && (!g.ws || mn * want * 4 > static_cast<double>(g.ws_bytes))) break;
       // two groups of 128 k per range at least, and no more ranges than fill the chip twice
-      if (want > 1 && (per < 2 || tiles * want > 2 * CUS * c.occ)) break;
+      if (want > least && want > 1 && (per < 2 || tiles * want > 2 * CUS * c.occ)) break;
       // the most workgroups a CU gets
       const double share = static_cast<double>((tiles * want + CUS - 1) / CUS);
       const int ktiles = want > 1 ? 4 * per : (g.K + 31) / 32, ke = want > 1 ? 0 : e;
       double t = share * (ktiles * c.ktile + c.fixed + (ke >= 0 ? c.epi[ke] : 0.0)) + c.call;
       if (want > 1)
         t += sc.fixed + mn * (sc.per_partial * want + (e > 0 ? sc.epi[e - 1] : 0.0)) + sc.range * want;
+      if (want < least) t += 1e9;  // only where nothing reaches the ranges asked for
       if (best.bm == 0 || t < best_t) {
         best = Choice{c.bm, c.bn, want, staged};
         best_t = t;

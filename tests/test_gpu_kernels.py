@@ -331,6 +331,37 @@ def test_gemm_f32_rounding(akc, bkc, M, N, K):
     assert err <= 2.0**-24 * np.sqrt((256 + K / 512) / 6), err
 
 
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0)])
+@pytest.mark.parametrize("M,N,K,ranges", [(2024, 960, 5120, 8), (352, 3272, 7168, 8), (3152, 1008, 3968, 3),
+                                          (536, 5488, 2944, 2), (96, 264, 16384, 16)])
+def test_gemm_f32_result_rounding(akc, bkc, M, N, K, ranges):
+    """fp32 results of few tiles of bf16 operands, given a workspace: no less exact than
+    256-row tiles split until 192 workgroups run (or 128-row tiles in ranges of
+    1024 k), which is rebuilt here: a product without workspace per range, summed
+    in order in fp32.  Both errors are norms of M N independent ones, whose ratio
+    has a standard deviation of about 1 / sqrt(M N): 2 % is more than three."""
+    r = U.rng(M + N + K)
+    Am = U.rep(r.standard_normal((M, K) if akc else (K, M)), "bf16")
+    Bm = U.rep(r.standard_normal((N, K) if bkc else (K, N)), "bf16")
+    dA, dB, dC, ws = U.dev(Am, "bf16"), U.dev(Bm, "bf16"), U.empty((M, N), "f32"), U.empty(16 << 20, "f32")
+    A.atom_k_gemm(A.ATOM_BF16, akc, bkc, A.ATOM_EPI_STORE_F32, M, N, K, U.ptr(dA), Am.shape[1], U.ptr(dB),
+                  Bm.shape[1], U.ptr(dC), N, stream=stream(), ws=U.ptr(ws), ws_bytes=64 << 20)
+    step = (K // 32 + ranges - 1) // ranges * 32
+    total = None
+    for k0 in range(0, K, step):
+        k1 = min(K, k0 + step)
+        a = (dA[:, k0:k1] if akc else dA[k0:k1]).contiguous()
+        b = (dB[:, k0:k1] if bkc else dB[k0:k1]).contiguous()
+        part = U.empty((M, N), "f32")
+        A.atom_k_gemm(A.ATOM_BF16, akc, bkc, A.ATOM_EPI_STORE_F32, M, N, k1 - k0, U.ptr(a), a.shape[1], U.ptr(b),
+                      b.shape[1], U.ptr(part), N, stream=stream())
+        U.sync()
+        total = part if total is None else total + part
+    ref = (dA if akc else dA.T).double() @ (dB.T if bkc else dB).double().contiguous()
+    err, split = float((dC - ref).norm()), float((total - ref).norm())
+    assert err <= 1.02 * split, (err, split)
+
+
 def test_gemm_rejects_unsupported_shapes():
     t = U.empty((64, 64), "bf16")
     with pytest.raises(A.AtomError):  # K not a multiple of 8
