@@ -79,3 +79,13 @@ extern "C" int atom_k_attn_bwd_noalloc(int dtype, const void* qkv, const void* o
   if (e == hipSuccess) return ATOM_OK;
   return e == hipErrorInvalidValue ? ATOM_EINVAL : ATOM_EHIP;
 }
+
+// The variants a problem takes (tests): 1 and 2 the forward of 64-row
+// workgroups and its split, 4 and 8 the backward's.
+extern "C" int atom_attn_choice(int B, int T, int H, int dh) {
+  using namespace atom::attn;
+  const bool sf = dh == 64 ? small_fwd<64>(B, T, H) : small_fwd<128>(B, T, H);
+  const bool sb = dh == 64 ? small_bwd<64>(B, T, H) : small_bwd<128>(B, T, H);
+  const bool kf = dh == 64 ? split_fwd<64>(B, T, H) : split_fwd<128>(B, T, H);
+  return (sf ? 1 : 0) | (sf && kf ? 2 : 0) | (sb ? 4 : 0) | (sb && split_bwd(B, T, H) ? 8 : 0);
+}

@@ -1525,14 +1525,22 @@ struct ACfg {
 };
 
 // Where the small variants (64-row workgroups) are taken; n64 = 64-row blocks
-// of all heads, times in us of forward + backward, large variants -> small.
-// Forward (four waves of 16 queries): d_h 128 up to one workgroup per CU (T 1000, 16 heads, n64 256: 85.7 ->
-// 82.6; n64 288 at T 1500 118.9 -> 122.1, 1280 254.6 -> 268.2); d_h 64, where
-// five share a CU, up to five per CU (n64 1280: 150.7 -> 146.0, 768: 125.5 ->
-// 118.3; 1536 even, 3072 298.1 -> 303.3).
+// of all heads, times in us, large variants -> small, of forward + backward
+// unless said otherwise.
+// Forward (four waves of 16 queries): d_h 128 up to one workgroup per CU (T
+// 1000, 16 heads, n64 256: 85.7 -> 82.6; n64 288 at T 1500 118.9 -> 122.1, 1280
+// 254.6 -> 268.2); d_h 64, where five share a CU, up to five per CU (T 2048,
+// n64 1280: 150.7 -> 146.0, 768: 125.5 -> 118.3; 1536 even, 3072 298.1 ->
+// 303.3), but three where heads have 65 to 512 rows: there the 128-row
+// workgroups have short chains too, and few heads of whole 128-row blocks
+// leave them little idle (forward alone: T 256, n64 736 / 936 / 1012: 8.8 ->
+// 8.1, 9.6 -> 11.7, 10.0 -> 12.0; T 333, 768 / 1134: 10.9 -> 8.3, 13.4 -> 15.8;
+// T 200, 1156: 11.0 -> 13.7; T 64, 1024 and T 1000, 1024 gain 28 and 16 %).
 template <int DH>
 bool small_fwd(int B, int Tn, int H) {
-  return static_cast<int64_t>(B) * H * ((Tn + 63) / 64) <= (DH == 128 ? 256 : 1280);
+  const int64_t n64 = static_cast<int64_t>(B) * H * ((Tn + 63) / 64);
+  if (DH == 128) return n64 <= 256;
+  return n64 <= (Tn > 64 && Tn <= 512 ? 768 : 1280);
 }
 // Backward: while dK/dV and dQ side by side take at most two rounds of the
 // resident workgroups (two per CU at d_h 128, three at d_h 64): d_h 128, T

@@ -113,3 +113,15 @@ def gemm_choice(dtype, akc, bkc, epi, M, N, K, ws_bytes=0):
     f.argtypes, f.restype = [ctypes.c_int] * 7 + [ctypes.c_uint64, ctypes.c_void_p], None
     f(dt_code(dtype), akc, bkc, epi, M, N, K, ws_bytes, ctypes.addressof(out))
     return tuple(out)
+
+
+def attn_choice(B, T, H, dh):
+    """Variants a bf16 attention problem takes: small forward, its split, small backward, its split."""
+    import ctypes
+
+    from paper_2403_10504_amd import atom as A
+
+    f = A.lib().atom_attn_choice
+    f.argtypes, f.restype = [ctypes.c_int] * 4, ctypes.c_int
+    bits = f(B, T, H, dh)
+    return tuple(bool(bits >> i & 1) for i in range(4))

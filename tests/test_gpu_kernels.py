@@ -454,6 +454,14 @@ def test_attention_fwd_bwd(dtype, B, T, H, dh):
         assert U.rel_err(got[:, :, sl], dqkv_ref[:, :, sl]) < tol, part
 
 
+@pytest.mark.parametrize("T,BH,small", [(64, 1280, True), (64, 1281, False), (128, 384, True), (128, 385, False),
+                                        (256, 192, True), (256, 193, False), (512, 96, True), (512, 97, False),
+                                        (576, 142, True), (576, 143, False)])
+def test_attention_forward_variant(T, BH, small):
+    """Where the forward of d_h 64 takes 64-row workgroups: up to five per CU, three at 65 to 512 rows."""
+    assert U.attn_choice(BH, T, 1, 64)[0] == small
+
+
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("T", [1, 63, 64, 65, 128, 129, 333, 2048, 2049])
 def test_attention_small_and_large_problems_agree(T, dh):
