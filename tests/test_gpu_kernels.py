@@ -107,7 +107,8 @@ def sampled_gemm_check(dtype, akc, bkc, M, N, K, ws_bytes=0, seed=0, rows=48):
 
 @pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0)])
 def test_gemm_large_tile_path(akc, bkc):
-    # >= 256 output tiles of 256x256 selects the large-tile kernel; ragged edges
+    # many output tiles with ragged edges (with both operands not k-contiguous,
+    # 4100 rows are no whole 16-byte chunks: the register-staged kernel)
     err, _ = sampled_gemm_check("bf16", akc, bkc, 4100, 4104, 264, seed=akc + 2 * bkc)
     assert err < 1e-4, err
 
@@ -120,39 +121,37 @@ ALL_EPI = [A.ATOM_EPI_STORE, A.ATOM_EPI_STORE_F32, A.ATOM_EPI_ACC_F32, A.ATOM_EP
 @pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
 @pytest.mark.parametrize("epi", ALL_EPI)
 def test_gemm_pipelined_path(akc, bkc, epi, K):
-    """bf16 problems with >= 256 tiles of 256x256 and k a multiple of 32 take the
-    four-stage direct-to-LDS kernels: sixteen waves for k = 352, and for k a
-    multiple of 128 (384: three loop trips; 128: the prologue's tiles only) the
-    four-wave kernel for every epilogue.  M and N end in partial tiles (ragged
-    by 8 and 24 rows) whose loads are clamped to the last valid rows and whose
-    epilogue takes the bounds-tested copy."""
+    """bf16 problems of many tiles and short k: k a multiple of 128 (384: three loop
+    trips; 128: the prologue's tiles only) and not (352: three tiles of 32 after
+    two trips).  M and N end in partial tiles (ragged by 8 and 24 rows) whose
+    loads are clamped to the last valid rows and whose epilogue takes the
+    bounds-tested copy."""
     check_pipelined(akc, bkc, epi, 4104, 4120, K, seed=akc + 2 * bkc + 4 * epi + K)
 
 
 @pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0)])
 @pytest.mark.parametrize("epi", [A.ATOM_EPI_STORE, A.ATOM_EPI_BIAS_GELU, A.ATOM_EPI_BIAS_RESID, A.ATOM_EPI_GELU_BWD])
 def test_gemm_pipelined_rotated_k(akc, bkc, epi):
-    """A whole number of 256x256 tiles per XCD (4096 x 4096: 256 tiles) makes
-    the four-wave kernel start each XCD's k loop at its own eighth of k
-    (k = 1152: 36 tiles of 32, offsets 0, 4, ..., 28) and takes the
-    branch-free epilogue in every tile."""
+    """256x256 tiles (a whole number per XCD: 256 tiles): each XCD starts its k loop
+    at its own eighth of k (k = 1152: 36 tiles of 32, offsets 0, 4, ..., 28), and
+    every tile takes the branch-free epilogue."""
+    assert U.gemm_choice("bf16", akc, bkc, epi, 4096, 4096, 1152)[:4] == (0, 256, 256, 1)
     check_pipelined(akc, bkc, epi, 4096, 4096, 1152, seed=100 + akc + 2 * bkc + 4 * epi)
 
 
 @pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0)])
 @pytest.mark.parametrize("M,N,K,epi", [
-    (3072, 4096, 1024, A.ATOM_EPI_BIAS_GELU),  # 192 tiles: four waves, no split
+    (3072, 4096, 1024, A.ATOM_EPI_BIAS_GELU),  # 192 tiles of 256x256: no split
     (3072, 4096, 1024, A.ATOM_EPI_GELU_BWD),
-    (2048, 2048, 4096, A.ATOM_EPI_STORE),  # 64 tiles: four splits of k
-    (1544, 1032, 2048, A.ATOM_EPI_ACC_F32),  # 35 ragged tiles: eight splits
+    (2048, 2048, 4096, A.ATOM_EPI_STORE),  # 64 tiles
+    (1544, 1032, 2048, A.ATOM_EPI_ACC_F32),  # 35 ragged tiles
     (1544, 1032, 2048, A.ATOM_EPI_STORE_F32),
-    (3072, 768, 16384, A.ATOM_EPI_STORE),  # 36 tiles: eight splits would overflow 64 MB, so four
+    (3072, 768, 16384, A.ATOM_EPI_STORE),  # 36 tiles; 64 MB hold seven splits at most
 ])
 def test_gemm_four_wave_few_tiles(akc, bkc, M, N, K, epi):
-    """Fewer 256x256 tiles than CUs: the four-wave kernel takes problems from
-    192 tiles on as they are, and fewer tiles over 2-16 ranges of k whose fp32
-    partial sums splitk_reduce adds in order (as many splits as bring the
-    workgroups to 192, or as the workspace holds if that leaves 96)."""
+    """Fewer 256x256 tiles than CUs, with a workspace: smaller tiles, or ranges of k
+    whose fp32 partial sums splitk_reduce adds in order (store epilogues, as
+    many as the workspace holds)."""
     seed = 200 + akc + 2 * bkc + 4 * epi + M
     check_pipelined(akc, bkc, epi, M, N, K, seed=seed, ws_bytes=64 << 20)
     if epi == A.ATOM_EPI_STORE_F32:
@@ -183,7 +182,7 @@ def check_pipelined(akc, bkc, epi, M, N, K, seed, ws_bytes=0):
                   U.ptr(dbias), U.ptr(dres), U.ptr(daux), N, stream(), ws=U.ptr(dws) if ws_bytes else None,
                   ws_bytes=ws_bytes)
     U.sync()
-    pick = np.sort(np.unique(np.concatenate([U.rng(7).choice(M, 40, replace=False), [M - 9, M - 1]])))
+    pick = np.sort(np.unique(np.concatenate([U.rng(7).choice(M, min(40, M), replace=False), [M - 9, M - 1]])))
     acc = (Am if akc else Am.T)[pick].astype(np.float64) @ (Bm.T if bkc else Bm).astype(np.float64)
     got = U.host(dC)[pick]
     if epi == A.ATOM_EPI_BIAS_GELU:
@@ -210,10 +209,10 @@ def check_pipelined(akc, bkc, epi, M, N, K, seed, ws_bytes=0):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (65, 68, 40), (31, 36, 136), (129, 260, 264), (520, 392, 520)])
 def test_gemm_direct_load_edges(dtype, M, N, K):
-    """The direct-load kernel at the edges of its small tiles (64 and 128 rows in
-    bf16, 32 and 64 in fp32), with k ending inside a tile of 32 and inside a
-    group of 128 (the chunks past k read zeros), and row counts that only a
-    k-contiguous operand may have.  Tolerances as for test_gemm_layouts."""
+    """The direct-load kernel at the edges of its smallest tiles (64 rows in bf16, 32
+    in fp32), with k ending inside a tile of 32 and inside a group of 128 (the
+    chunks past k read zeros), and row counts that only a k-contiguous operand
+    may have.  Tolerances as for test_gemm_layouts."""
     for akc, bkc in ((1, 1), (1, 0), (0, 0), (0, 1)):
         Mr, Nr = (M if akc else (M + 7) // 8 * 8), (N if bkc else (N + 7) // 8 * 8)
         err, tol = gemm_case(dtype, akc, bkc, Mr, Nr, K, A.ATOM_EPI_STORE, seed=M + N + K + akc + 2 * bkc)
@@ -233,6 +232,46 @@ def test_gemm_direct_load_tiles(akc, bkc, M, N, K, ws, epi):
     check_pipelined(akc, bkc, epi, M, N, K, seed=300 + akc + 2 * bkc + 4 * epi + K, ws_bytes=ws)
 
 
+# The training step's layouts and epilogues (forward, data and weight gradient).
+STEP_COMBOS = [(1, 1, A.ATOM_EPI_STORE), (1, 1, A.ATOM_EPI_STORE_F32), (1, 1, A.ATOM_EPI_BIAS),
+               (1, 1, A.ATOM_EPI_BIAS_GELU), (1, 1, A.ATOM_EPI_BIAS_RESID), (1, 0, A.ATOM_EPI_STORE),
+               (1, 0, A.ATOM_EPI_STORE_F32), (1, 0, A.ATOM_EPI_GELU_BWD), (0, 0, A.ATOM_EPI_STORE),
+               (0, 0, A.ATOM_EPI_STORE_F32), (0, 0, A.ATOM_EPI_ACC_F32)]
+STORE_COMBOS = [c for c in STEP_COMBOS if c[2] <= A.ATOM_EPI_ACC_F32]
+
+
+@pytest.mark.parametrize("akc,bkc,epi", STEP_COMBOS)
+@pytest.mark.parametrize("tile,M,N,K", [
+    # rows and columns ragged and k ending inside a group of 128, then whole tiles and whole groups
+    ((256, 256), 3920, 3144, 856), ((256, 256), 3840, 3328, 896),
+    ((256, 192), 2232, 3736, 1224), ((256, 192), 3840, 3264, 640),
+    ((256, 128), 3472, 1176, 1072), ((256, 128), 3328, 1280, 1152),
+    ((128, 128), 2808, 1224, 136), ((128, 128), 1920, 1664, 256),
+    ((64, 64), 24, 32, 712), ((64, 64), 64, 128, 384)])
+def test_gemm_every_tile(akc, bkc, epi, tile, M, N, K):
+    """Each bf16 tile of the direct-load kernel under every epilogue of the training
+    step, by the bounds-tested and the branch-free copy of the epilogue, with
+    and without a k tail."""
+    assert U.gemm_choice("bf16", akc, bkc, epi, M, N, K)[:4] == (0, *tile, 1)
+    check_pipelined(akc, bkc, epi, M, N, K, seed=400 + akc + 2 * bkc + 4 * epi + K)
+
+
+@pytest.mark.parametrize("akc,bkc,epi", STORE_COMBOS)
+@pytest.mark.parametrize("tile,M,N,K", [
+    ((256, 256), 1456, 2728, 3736), ((256, 256), 2304, 2048, 3456),
+    ((256, 192), 648, 2184, 7800), ((256, 192), 1024, 2112, 5120),
+    ((256, 128), 936, 1328, 4968), ((256, 128), 512, 2816, 5760),
+    ((128, 128), 2704, 96, 4968), ((128, 128), 2816, 128, 5248),
+    ((64, 64), 16, 120, 1840), ((64, 64), 64, 64, 6144)])
+def test_gemm_every_tile_split(akc, bkc, epi, tile, M, N, K):
+    """The same tiles over several ranges of k (the last one short in the first of
+    each pair), their partials summed by splitk_reduce."""
+    ws = 64 << 20
+    staged, bm, bn, splits, _ = U.gemm_choice("bf16", akc, bkc, epi, M, N, K, ws)
+    assert (staged, bm, bn) == (0, *tile) and splits > 1
+    check_pipelined(akc, bkc, epi, M, N, K, seed=500 + akc + 2 * bkc + 4 * epi + K, ws_bytes=ws)
+
+
 @pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
 @pytest.mark.parametrize("K", [8, 32, 40, 64, 96, 104, 160, 200, 224])
 def test_gemm_k_tail(akc, bkc, K):
@@ -241,6 +280,16 @@ def test_gemm_k_tail(akc, bkc, K):
     for dtype, M, N in (("bf16", 264, 200), ("bf16", 2808, 1224), ("f32", 68, 100)):
         err, tol = gemm_case(dtype, akc, bkc, M, N, K, A.ATOM_EPI_STORE, seed=M + K + akc + 2 * bkc)
         assert err < tol, (dtype, M, err)
+
+
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("epi", ALL_EPI)
+@pytest.mark.parametrize("M,N,K", [(2244, 332, 280), (2220, 324, 384)])
+def test_gemm_f32_large_tile(akc, bkc, epi, M, N, K):
+    """The fp32 64x64 tile: every layout and epilogue, ragged, with and without a k tail."""
+    assert U.gemm_choice("f32", akc, bkc, epi, M, N, K)[:4] == (0, 64, 64, 1)
+    err, tol = gemm_case("f32", akc, bkc, M, N, K, epi, seed=M + K + akc + 2 * bkc + 4 * epi)
+    assert err < tol, err
 
 
 def test_gemm_choice_of_short_k():
@@ -267,6 +316,18 @@ def test_gemm_unaligned_large(akc, bkc, epi):
     M, N, K = 3428, 8094, 456
     assert U.gemm_choice("bf16", akc, bkc, epi, M, N, K) == (1, 256, 256, 1, 0)
     check_pipelined(akc, bkc, epi, M, N, K, seed=600 + akc + 2 * bkc + 4 * epi)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
+def test_gemm_unaligned_split_k(dtype, akc, bkc):
+    """The register-staged kernel's split over k, whose sum takes columns one by one
+    where N is no multiple of four."""
+    M, N, K, ws = 136, 390 if dtype == "bf16" else 391, 8192, 64 << 20
+    staged, _, _, splits, _ = U.gemm_choice(dtype, akc, bkc, A.ATOM_EPI_STORE_F32, M, N, K, ws)
+    assert staged and splits > 1
+    err, _ = sampled_gemm_check(dtype, akc, bkc, M, N, K, ws_bytes=ws, seed=akc + 2 * bkc, rows=M)
+    assert err < (1e-4 if dtype == "bf16" else 1e-5), err
 
 
 @pytest.mark.parametrize("N", [5496, 5504])
@@ -373,7 +434,9 @@ def test_gemm_rejects_unsupported_shapes():
 # ----------------------------------------------------------------- LayerNorm
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("rows,d", [(37, 256), (130, 768), (17, 320), (5, 4096), (3, 5120), (4100, 256),
-                                    (300, 2048), (1031, 5120), (77, 1088), (16, 8192), (41, 1024)])
+                                    (300, 2048), (1031, 5120), (77, 1088), (16, 8192), (41, 1024),
+                                    # 512 blocks of rows, the last one partial: 256 threads up to 4096 columns
+                                    (4091, 2112), (4091, 3072), (4091, 4096)])
 def test_layernorm_fwd_bwd(dtype, rows, d):
     r = U.rng(rows + d)
     x = (r.standard_normal((rows, d)) * 2 + 0.5).astype(np.float32)
@@ -413,7 +476,9 @@ def test_layernorm_fwd_bwd(dtype, rows, d):
 # query tiles through the two-stage pipelines) at both head sizes; B*H a
 # multiple of 8 takes the per-XCD split of the heads in the work-item order
 ATTN_CASES = [(2, 100, 2, 64), (1, 128, 3, 128), (1, 1, 1, 64), (2, 200, 1, 128), (1, 64, 2, 64), (1, 257, 1, 64),
-              (1, 1000, 2, 128), (2, 600, 1, 64), (2, 300, 4, 64), (1, 520, 16, 128), (4, 130, 6, 64)]
+              (1, 1000, 2, 128), (2, 600, 1, 64), (2, 300, 4, 64), (1, 520, 16, 128), (4, 130, 6, 64)] + [
+    # above every rule for small problems: the 128-row kernels in forward and backward
+    (36, 130, 12, 64), (18, 333, 12, 64), (18, 130, 10, 128), (11, 333, 8, 128)]
 
 
 def attn_inputs(B, T, H, dh, dtype, seed):
@@ -452,6 +517,14 @@ def test_attention_fwd_bwd(dtype, B, T, H, dh):
     for part in range(3):
         sl = slice(part * d, (part + 1) * d)
         assert U.rel_err(got[:, :, sl], dqkv_ref[:, :, sl]) < tol, part
+
+
+def test_attention_cases_take_every_variant():
+    """The cases above reach the split and unsplit small kernels and the large ones at both head sizes."""
+    for dh in (64, 128):
+        seen = {U.attn_choice(*c) for c in ATTN_CASES if c[3] == dh}
+        for f in (0, 2):  # forward, backward
+            assert {v[f:f + 2] for v in seen} == {(False, False), (True, False), (True, True)}, (dh, f)
 
 
 @pytest.mark.parametrize("T,BH,small", [(64, 1280, True), (64, 1281, False), (128, 384, True), (128, 385, False),
