@@ -42,9 +42,9 @@ HBM_PEAK_GBS = 8000.0
 # --copy-calibration 2147483648`, each scaled by what the counter reads for
 # the plain copy kernel of known size (profiles/gemm_wgrad_6.7b_hbm_traffic.md).
 # Valid only for the kernel sources it was measured on.
-WGRAD_TRAFFIC = {"sources_sha256": "5b2c7ed08ef49c4e14822aaf57262fccd09a2efe914ec142e5b6281a7b7cd87c",
-                 "bytes_per_launch": 725832891}
-TRAFFIC_SOURCES = ("gemm.hip", "gemm_dl.h", "common.h", "launch.h")
+WGRAD_TRAFFIC = {"sources_sha256": "fdb77e2684147a47a0610f98eb910edd0690dbb2d74258b31162bf977a991bdd",
+                 "bytes_per_launch": 725825619}
+TRAFFIC_SOURCES = ("gemm.hip", "gemm_dl.h", "gemm_dl_256.hip", "common.h", "launch.h")
 
 
 def wgrad_kernel_name(cfg, epi):

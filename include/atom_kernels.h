@@ -8,6 +8,13 @@
  * ATOM_OK, ATOM_EINVAL (shape, alignment or dtype not supported) or ATOM_EHIP
  * (launch failed).  dtype is ATOM_F32 or ATOM_BF16 (bf16 tensors are raw
  * 16-bit patterns); accumulation is fp32 in every kernel.
+ *
+ * A call repeats its results bit for bit.  The order of its sums, and so their
+ * last bits, follows from all of its sizes: tiles, splits and work per thread
+ * are chosen by them (a product by M, N, K, epilogue and workspace; a head's
+ * attention beyond 256 rows by the number of heads in the call; a row's
+ * LayerNorm gradient at 2048 < d <= 4096 by the number of rows; column sums by
+ * the number of rows).  Rows of different calls are equal to rounding only.
  */
 #ifndef ATOM_KERNELS_H
 #define ATOM_KERNELS_H

@@ -458,7 +458,7 @@ __global__ void __launch_bounds__(64 * NW * KS, WPS)
     for (int c = 0; c < NCT; ++c) acc_o[g][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 
-  // load q of a thread: chunk q*256 + tid of the tile (row, slot).  Its
+  // load q of a thread: chunk q * NT + tid of the tile (row, slot).  Its
   // sources for key tile 0 are computed once; a whole tile adds the tile's
   // row offset (a wave-uniform product), only the last, partial tile clamps
   // its rows to the last key.
@@ -1011,10 +1011,10 @@ __device__ __forceinline__ float row_dot(const Frag<bf16_t> (&x)[NS], const Frag
 template <int DH>
 __device__ __forceinline__ int dsw(int r);
 
-// Launch bounds of the backward kernels: at d_h 64 four waves per SIMD (108
-// registers; two eight-wave workgroups per CU: 264 against 291 us for the
-// whole backward at GPT-3 Small's shape), at d_h 128 two (244 and 174
-// registers, one workgroup per CU; 128 registers would spill).
+// Launch bounds of the backward kernels: at d_h 64 four waves per SIMD (dK/dV
+// 128 registers, two of them spilled, dQ 118; two eight-wave workgroups per CU:
+// 264 against 291 us for the whole backward at GPT-3 Small's shape), at d_h 128
+// two (246 and 208 registers, one workgroup per CU; 128 registers would spill).
 //
 // OWN_D: D is computed here from O and dO, for every query the workgroup
 // visits, into d_own ([queries from the first tile on], LDS); otherwise it is
@@ -1529,7 +1529,9 @@ struct ACfg {
 // unless said otherwise.
 // Forward (four waves of 16 queries): d_h 128 up to one workgroup per CU (T
 // 1000, 16 heads, n64 256: 85.7 -> 82.6; n64 288 at T 1500 118.9 -> 122.1, 1280
-// 254.6 -> 268.2); d_h 64, where five share a CU, up to five per CU (T 2048,
+// 254.6 -> 268.2; short heads would gain beyond it, forward alone: T 64, n64
+// 288 / 512: 7.2 -> 6.0, 8.3 -> 6.7, T 333, 288 / 576: 11.0 -> 9.7, 13.5 -> 11.6,
+// T 2048, 288: 39.5 -> 44.9); d_h 64, where five share a CU, up to five per CU (T 2048,
 // n64 1280: 150.7 -> 146.0, 768: 125.5 -> 118.3; 1536 even, 3072 298.1 ->
 // 303.3), but three where heads have 65 to 512 rows: there the 128-row
 // workgroups have short chains too, and few heads of whole 128-row blocks
@@ -1574,7 +1576,11 @@ bool split_fwd(int B, int Tn, int H) {
 // / 192 / 256 at d_h 128: 116.5 -> 103.7, 132.4 -> 112.9, 124.5 -> 104.8; T
 // 1000, n64 256 / 320: 67.9 -> 60.3, 81.5 -> 82.3; T 512, n64 128 / 256: 37.4 ->
 // 35.0, 40.4 -> 41.5; T 333, n64 192 / 288: 32.0 -> 28.2, 35.5 -> 39.1; T 200,
-// n64 192: 24.3 -> 25.6; d_h 64 alike).
+// n64 192: 24.3 -> 25.6).  At d_h 64, and at d_h 128 for long heads, it would
+// gain a little further (backward alone: d_h 64, T 2048, n64 320 / 384 / 448:
+// 60.8 -> 50.7, 62.5 -> 58.0, 68.4 -> 66.9; T 1000, 320 / 384: 33.1 -> 31.0, 34.7
+// -> 35.7; T 512, 256 / 320: 18.5 -> 18.0, 19.7 -> 21.6; T 333, 288: 15.1 -> 16.0;
+// d_h 128, T 2048, 320 / 384 / 448: 97.7 -> 88.1, 98.2 -> 97.8, 109.4 -> 117.2).
 inline bool split_bwd(int B, int Tn, int H) {
   return Tn > 256 && static_cast<int64_t>(B) * H * ((Tn + 63) / 64) <= (Tn >= 1000 ? 256 : 192);
 }

@@ -244,7 +244,8 @@ gemm_dl_kernel(GemmArgs g) {
   for (int q = 0; q < OB::LPT; ++q) srb[q].init(static_cast<const T*>(g.B), g.ldb, n0, g.N, q * NT + tid);
   // k tiles of this workgroup: kquads groups of four per split, the rest in
   // the last one (the launcher leaves none empty).  With TAIL the last group
-  // may be short: only the tiles that hold k are loaded and multiplied.
+  // may be short: only the tiles that hold k are loaded and multiplied
+  // (4096x8192x576: 49.0 us with a whole last group, 47.0; 8192x8192x352: 81, 78).
   const int quads = (g.K + 4 * BK - 1) / (4 * BK);
   const int kbase = split * g.kquads * 4;
   const int nk4 = min(g.kquads, quads - split * g.kquads) * 4;
